@@ -134,17 +134,13 @@ inline int raster_grid(const SetK& set, int tw, int th, bool split) {
 // (consecutive threads on consecutive rows) and the wave's reads (its 8
 // rows of one splat) both touch consecutive words.
 constexpr int kBatch = 64;  // splats per batch: one per lane
-// The forward stages no backward terms: its smaller LDS footprint lets more
-// of its one-wave workgroups share a CU.
-template <bool DEPTH, bool BWD>
+template <bool DEPTH>
 struct StageT {
   float4 hdr[kBatch];      // qa', r, g, b
   float2 rows[kBatch][8];  // per quadrant row: log2(o) - qc' dy^2, and dx - qb dy at the
                            // quadrant's first column
   uint32_t pos[kBatch];    // the splat's position in the tile's list (as the kernel counts it)
   float dep[DEPTH ? kBatch : 1];  // camera-space depth (mesh depth test only)
-  float4 aux[BWD ? kBatch : 1];   // qb, qc', dy at the quadrant's first row, 1 / opacity
-  uint32_t gid[BWD ? kBatch : 1];  // Gaussian index
 };
 
 // The LDS operands of staged splats k and k + 1 at one pixel row: the row
@@ -155,7 +151,7 @@ struct PairOps {
   float d0, d1;  // depths (mesh depth test only)
 };
 template <bool DEPTH, int K>
-__device__ __forceinline__ void read_pair(const StageT<DEPTH, false>& S, std::integral_constant<int, K>,
+__device__ __forceinline__ void read_pair(const StageT<DEPTH>& S, std::integral_constant<int, K>,
                                           int row, PairOps& o) {
   o.q0 = S.rows[K][row];
   o.q1 = S.rows[K + 1][row];
@@ -217,62 +213,77 @@ __device__ __forceinline__ SplatRec load_splat(const gs_splat* __restrict__ spla
   return r;
 }
 
-// Staging of one batch, called by every lane of the wave (lane j holds the
-// batch's j-th splat when `valid`): whether the splat's footprint reaches
-// pixel rows hy0..hy1 of the quadrant whose top-left pixel is (qx0, qy0)
-// (all 8 rows, or the band the wave composites), and if so its
-// parameters, list position `pos` and per-row weight terms (with BWD also
-// the backward's terms and the Gaussian index g), written
-// at its rank among the batch's hits.  The reach test uses the record's
-// pixel bbox, which preprocess rounded outwards from the opacity-aware
-// footprint.  DEPTH also stages the depth.  An odd count is padded with
-// one splat that no pixel takes (its log2 weight is -inf and it hides
-// nothing), so the forward walk can take the splats in pairs without a
-// test.  Returns the number of hits.
-template <bool DEPTH, bool BWD>
-__device__ __forceinline__ int stage_batch(StageT<DEPTH, BWD>& S, bool valid, const SplatRec& r,
-                                           uint32_t g, uint32_t pos, int qx0, int qy0,
-                                           int lane, int hy0, int hy1) {
-  const float4 a = r.a, b = r.b;
-  const float c = r.c;
-  const float mx = a.x, my = a.y, qb = a.w;  // mean relative to the bbox corner (px0, py0)
-  const float qa_ = a.z * kHalfLog2e, qc_ = b.x * kHalfLog2e;
-  const float lo = log2f(b.y);
+// A splat's terms relative to one quadrant (top-left pixel (qx0, qy0)), as
+// the lane that holds the record computes them: the row terms follow from
+// lo, qc', qb, uy and ux by the two expressions of term(), the same in
+// both kernels, so the backward's skip decisions match the forward's.
+struct QuadTerms {
+  float qa, qb, qc;  // qa log2e/2, qb, qc log2e/2
+  float lo;          // log2(o)
+  float ux, uy;      // dx at the quadrant's first column, dy at its first row
+  __device__ __forceinline__ QuadTerms(const SplatRec& r, int qx0, int qy0) {
+    qa = r.a.z * kHalfLog2e;
+    qb = r.a.w;
+    qc = r.b.x * kHalfLog2e;
+    lo = log2f(r.b.y);
+    // pixel offsets from the mean: exact integer differences from the bbox
+    // corner (px0, py0), minus the mean's (small) offset from it
+    ux = (float)(qx0 - (int)(r.lo & 0xFFFFu)) + 0.5f - r.a.x;
+    uy = (float)(qy0 - (int)(r.lo >> 16)) + 0.5f - r.a.y;
+  }
+  // log2(o) - qc' dy^2, and dx - qb dy at the first column, in row rr
+  __device__ __forceinline__ float2 term(int rr) const {
+    const float dy = uy + (float)rr;
+    return make_float2(fmaf(-qc, dy * dy, lo), fmaf(-qb, dy, ux));
+  }
+  // the terms of the quadrant's 8 rows
+  __device__ __forceinline__ void rows(float2 (&out)[8]) const {
+    float4* dst = reinterpret_cast<float4*>(out);
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      const float2 p = term(2 * rr), q = term(2 * rr + 1);
+      dst[rr] = make_float4(p.x, p.y, q.x, q.y);
+    }
+  }
+};
+
+// Whether the splat's footprint reaches pixel rows hy0..hy1 of the
+// quadrant at column qx0: the record's pixel bbox, which preprocess
+// rounded outwards from the opacity-aware footprint.
+__device__ __forceinline__ bool reaches(const SplatRec& r, int qx0, int hy0, int hy1) {
   const int px0 = (int)(r.lo & 0xFFFFu), py0 = (int)(r.lo >> 16);
   const int px1 = (int)(r.hi & 0xFFFFu), py1 = (int)(r.hi >> 16);
-  const bool hit = valid && px0 <= qx0 + 7 && px1 >= qx0 && py0 <= hy1 && py1 >= hy0;
+  return px0 <= qx0 + 7 && px1 >= qx0 && py0 <= hy1 && py1 >= hy0;
+}
+
+// Forward staging of one batch, called by every lane of the wave (lane j
+// holds the batch's j-th splat when `valid`): the splats that reach pixel
+// rows hy0..hy1 of the quadrant (all 8 rows, or the band the wave
+// composites) are written at their rank among the batch's hits, with their
+// list position `pos` and per-row weight terms.  DEPTH also stages the
+// depth.  An odd count is padded with one splat that no pixel takes (its
+// log2 weight is -inf and it hides nothing), so the walk can take the
+// splats in pairs without a test.  Returns the number of hits.
+template <bool DEPTH>
+__device__ __forceinline__ int stage_batch(StageT<DEPTH>& S, bool valid, const SplatRec& r,
+                                           uint32_t pos, int qx0, int qy0, int lane, int hy0,
+                                           int hy1) {
+  const bool hit = valid && reaches(r, qx0, hy0, hy1);
   const uint64_t hits = ballot(hit);
   const int nh = __builtin_popcountll(hits);
   if (hit) {
     const int k = __builtin_popcountll(hits & ((1ull << lane) - 1ull));
-    S.hdr[k] = make_float4(qa_, b.z, b.w, c);
-    // pixel offsets from the mean: exact integer differences from the bbox
-    // corner, minus the mean's (small) offset from it
-    const float uy = (float)(qy0 - py0) + 0.5f - my;  // dy at the quadrant's first row
-    if constexpr (BWD) {  // only the backward's gradient terms and atomics read these
-      S.aux[k] = make_float4(qb, qc_, uy, 1.f / b.y);
-      S.gid[k] = g;
-    }
+    const QuadTerms q(r, qx0, qy0);
+    S.hdr[k] = make_float4(q.qa, r.b.z, r.b.w, r.c);
     S.pos[k] = pos;
     if constexpr (DEPTH) S.dep[k] = r.depth;
-    // log2(o) - qc' dy^2 and dx - qb dy at the first column, per row
-    const float ux = (float)(qx0 - px0) + 0.5f - mx;
-    float4* dst = reinterpret_cast<float4*>(S.rows[k]);
     if (hy1 - hy0 == 7) {  // the whole quadrant
-      float2 t[8];
-#pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const float dy = uy + (float)rr;
-        t[rr] = make_float2(fmaf(-qc_, dy * dy, lo), fmaf(-qb, dy, ux));
-      }
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr)
-        dst[rr] = make_float4(t[2 * rr].x, t[2 * rr].y, t[2 * rr + 1].x, t[2 * rr + 1].y);
+      q.rows(S.rows[k]);
     } else {  // a band of 2 or 4 rows starting at an even row: only its rows
+      float4* dst = reinterpret_cast<float4*>(S.rows[k]);
       for (int rr = hy0 - qy0; rr <= hy1 - qy0; rr += 2) {
-        const float dy0 = uy + (float)rr, dy1 = uy + (float)(rr + 1);
-        dst[rr >> 1] = make_float4(fmaf(-qc_, dy0 * dy0, lo), fmaf(-qb, dy0, ux),
-                                   fmaf(-qc_, dy1 * dy1, lo), fmaf(-qb, dy1, ux));
+        const float2 t0 = q.term(rr), t1 = q.term(rr + 1);
+        dst[rr >> 1] = make_float4(t0.x, t0.y, t1.x, t1.y);
       }
     }
   }
@@ -302,7 +313,7 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
                                                uint32_t* __restrict__ last,
                                                uint32_t* __restrict__ n_blend) {
   constexpr int QX = TW / 8, NQ = (TW / 8) * (TH / 8);
-  __shared__ StageT<MESH, false> S;
+  __shared__ StageT<MESH> S;
   int tile, q, band;
   if (!pick_unit<NQ, true>(blockIdx.x, set, ranges, tile, q, band)) return;
   int trow = tile / set.tiles_x;
@@ -359,8 +370,8 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
     if (!ballot(!done)) break;
     const int cnt = (int)min((uint32_t)kBatch, end - bs);
     __syncthreads();  // the previous batch's reads of S are done
-    int nh = stage_batch<MESH, false>(S, lane < cnt, r_cur, g_cur, bs - start + lane + 1, tx0,
-                                      ty0, lane, hy0, hy1);
+    int nh = stage_batch<MESH>(S, lane < cnt, r_cur, bs - start + lane + 1, tx0, ty0, lane, hy0,
+                               hy1);
     // an opaque 32-bit scalar, so that the walk's end tests stay one
     // scalar compare (the compiler otherwise compares the 64-bit mask)
     asm volatile("" : "+s"(nh));
@@ -454,12 +465,33 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
 // recovering T_i = T_{i+1} / (1 - alpha_i) from T_final.  With
 //   S_i = colour composited behind i (normalised by T_{i+1}),
 //   B_i = T_final / T_{i+1},
-// dC/dalpha_i = T_i (c_i - S_i - B_i bg) and dA/dalpha_i = T_i B_i.
-// Per splat the 9 partial derivatives are summed over each pixel row (8
-// lanes) with DPP; the last lane of each row stores its 9 sums to LDS,
-// lanes 0-8 each add up one value's 8 row sums and add it to the
-// Gaussian's 2-D gradient record: one float-atomic instruction per splat
-// and quadrant.
+// dL/dalpha_i = T_i (dC . (c_i - S_i - B_i bg) + dA B_i)
+//             = T_i (dC . c_i - R_i),  R_i = dC . S_i + B_i (dC . bg - dA),
+// and R needs no more than one fma per splat:
+//   R_{i-1} = R_i + alpha_i (dC . c_i - R_i).
+//
+// A splat's 9 gradient sums over the quadrant's 64 pixels are products with
+// matrices that do not depend on the splat: with w = alpha T the blend
+// weight and q = dL/de (e: the log2 weight),
+//   dL/drgb = sum_p w(p) dC(p),
+// and, as e is a quadratic in the pixel's offset (x, y) from a centre, the
+// other six follow from the moments sum_p q(p) x^a y^b, a + b <= 2.  So each
+// splat leaves its q and w of the 64 pixels in LDS, and once kGroup splats
+// are together 16 fp32 MFMAs (16x16x4) multiply the 16 features of the
+// pixels with the pixels' q and w.  The features are dC and the monomials
+// about each of the four quarters' centres, 16 in all, and a splat's sums
+// are formed from those about the centre nearest its mean, so that they
+// cancel little even for the smallest splats (sigma 0.55 px; moments about
+// the quadrant's centre made the gradients of such scenes 2-3 times less
+// accurate than per-pixel sums).
+//
+// Bound: vector and matrix issue (they share it: a variant without the MFMAs
+// saved their whole 32 cycles each).  Summing 9 values with DPP row shifts,
+// an LDS exchange and one atomic per splat took ~130 vector instructions per
+// (splat, quadrant) visit; here a visit takes ~27 and its share of a group
+// ~8 and 2.4 MFMAs, and one atomic instruction sends a group's 63 values.
+// Measured: 500k Gaussians at 800x800, 32x16 tiles, 247 -> 195 us; 32 views
+// of 4.5M, 16x8 tiles, 11.9 -> 9.7 ms; 20k at 250x190, 138 -> 91 us.
 //
 // Each 8x8 quadrant of a TW x TH tile is its own one-wave workgroup that
 // walks the tile's whole list (skipping splats that miss the quadrant), so
@@ -467,8 +499,39 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
 // here is heavy, and small workgroups balance it across the CUs far better
 // than one workgroup per tile.  A quadrant stages exactly the row terms the
 // forward kernel used for its pixels, so every skip decision matches.
+constexpr int kGroup = 7;         // splats per matrix product: 7 x 9 values fill one atomic
+constexpr int kPixStride = 68;    // floats per w / q row (64 pixels, padded: the rows of one
+                                  // 16-byte column lie in different banks)
+constexpr int kVals = 9;          // gradient values per splat
+constexpr int kSumStride = 12;    // floats per splat of its sums in LDS
+using f32x4 = __attribute__((ext_vector_type(4))) float;
+
+// Lanes 0..15 get x of lanes 16..31.
+__device__ __forceinline__ float next_row(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[1]);
+}
+
+// Lanes 0..31 get x of lanes 32..63.
+__device__ __forceinline__ float upper_half(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[1]);
+}
+
+// The staged splats of the backward walk, in walk order (back to front).
+constexpr int kStaged = 32;
+struct StageB {
+  float4 hdr[kStaged];      // qa', r, g, b
+  float2 rows[kStaged][8];  // as in StageT
+  float4 aux[kStaged];      // qb, qc', dy at the quadrant's first row, 1 / opacity
+  uint32_t gid[kStaged];    // Gaussian index
+  uint32_t ctr[kStaged];    // its moments' centre: bit 0, x = +2 (else -2); bit 1, y
+};
+
 template <int TW, int TH>
-__global__ __launch_bounds__(64) void k_raster_bwd(const gs_splat* __restrict__ splats,
+// at least 2 waves per SIMD: the compiler then keeps the MFMA accumulators in
+// plain VGPRs (with a 1-wave budget it uses accumulation VGPRs and moves)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_raster_bwd(const gs_splat* __restrict__ splats,
                                                    const uint32_t* __restrict__ values,
                                                    const uint32_t* __restrict__ ranges,
                                                    SetK set, int W, int H,
@@ -478,9 +541,10 @@ __global__ __launch_bounds__(64) void k_raster_bwd(const gs_splat* __restrict__ 
                                                    const float* __restrict__ dL_dimage,
                                                    float* __restrict__ grad2d) {
   constexpr int QX = TW / 8, NQ = (TW / 8) * (TH / 8);
-  __shared__ StageT<false, true> S;
-  // per 8-lane group (pixel row): the 9 gradient sums of up to two splats
-  __shared__ __attribute__((aligned(16))) float s_red[8][24];
+  __shared__ StageB S;
+  // rows 0..kGroup-1: q of the group's splats, rows 8..8+kGroup-1: w; then
+  // (rows read) the group's kGroup x 9 sums
+  __shared__ __attribute__((aligned(16))) float s_p[16 * kPixStride];
   int tile, q, band;
   if (!pick_unit<NQ, false>(blockIdx.x, set, ranges, tile, q, band)) return;
   int trow = tile / set.tiles_x;
@@ -499,9 +563,9 @@ __global__ __launch_bounds__(64) void k_raster_bwd(const gs_splat* __restrict__ 
   const int lx = lane & 7, row = lane >> 3;
   const int px = tx0 + lx, py = ty0 + row;
   const bool inside = px < W && py < H;
-  const float lxf = (float)lx, rowf = (float)row;
+  const float lxf = (float)lx;
   const uint32_t start = ranges[2 * tile];
-  const float log2_tau = set.log2_tau;
+  const float log2_tau = set.log2_tau, amax = set.amax;
 
   float T = 1.f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f, dA = 0.f;
   float b0 = set.bg[0], b1 = set.bg[1], b2 = set.bg[2];  // colour behind the Gaussians
@@ -523,120 +587,215 @@ __global__ __launch_bounds__(64) void k_raster_bwd(const gs_splat* __restrict__ 
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) nlast = max(nlast, shfl_u32(nlast, lane ^ d));
   nlast = __builtin_amdgcn_readfirstlane(nlast);
-  const float bgdot = dC0 * b0 + dC1 * b1 + dC2 * b2;
-  float S0 = 0.f, S1 = 0.f, S2 = 0.f, B = 1.f;
+  if (nlast == 0) return;
+  float R = dC0 * b0 + dC1 * b1 + dC2 * b2 - dA;
 
-  // batches cover positions [0, nlast) of the tile's range, last batch first
-  const int nb = (int)((nlast + kBatch - 1) / kBatch);
-  for (int bi = nb - 1; bi >= 0; --bi) {
-    const uint32_t bs = (uint32_t)bi * kBatch;
-    __syncthreads();
-    const int cnt = (int)min((uint32_t)kBatch, nlast - bs);
-    uint32_t g = 0;
-    SplatRec rec = {};
-    if (lane < cnt) {
-      g = values[start + bs + lane];
-      rec = load_splat(splats, g);
+  // The matrix of the pixels, in the layout of the MFMA's A operand: step t
+  // (0..15), lane (16 k + j) holds feature j of pixel 16 k + t.  With x, y the
+  // pixel's offset from the quadrant's centre and x-, x+ = x + 2, x - 2:
+  //   0: 1      1..3: dC     4..7: x-, x+, y-, y+
+  //   8..11: x-^2, x+^2, y-^2, y+^2    12..15: x- y-, x- y+, x+ y-, x+ y+
+  const int col = lane & 15, kq = lane >> 4;
+  float feat[16];
+  s_p[lane] = dC0;
+  s_p[kPixStride + lane] = dC1;
+  s_p[2 * kPixStride + lane] = dC2;
+  __syncthreads();
+  {
+    const int grp = col >> 2, var = col & 3;
+    const bool fx = grp == 3 || (grp > 0 && var < 2), fy = grp == 3 || (grp > 0 && var >= 2);
+    const float cx = (grp == 3 ? var >= 2 : var == 1) ? 2.f : -2.f;
+    const float cy = (var & 1) ? 2.f : -2.f;
+    // the feature is px(x) py(y), each 1, the offset or its square
+    auto power = [&](float d, bool on) { return on ? (grp == 2 ? d * d : d) : 1.f; };
+    const float yk = 2.f * (float)kq - 3.5f - cy;  // rows 2 k and 2 k + 1
+    const float py[2] = {power(yk, fy), power(yk + 1.f, fy)};
+    float pxs[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pxs[i] = power((float)i - 3.5f - cx, fx);
+    const bool colour = grp == 0 && var > 0;
+    const float4* src =
+        reinterpret_cast<const float4*>(s_p + (colour ? var - 1 : 0) * kPixStride + 16 * kq);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4 g = src[t];
+      const float gc[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        feat[4 * t + i] = colour ? gc[i] : pxs[(4 * t + i) & 7] * py[t >> 1];
     }
-    const int nh = stage_batch<false, true>(S, lane < cnt, rec, g, bs + lane, tx0, ty0, lane,
-                                            ty0, ty0 + 7);
+  }
+  __syncthreads();
+
+  // the value this lane sends for a group: value lane % 9 of its splat lane / 9
+  const int vslot = lane / kVals, vj = lane - vslot * kVals;
+  // Sums of the group's first `ns` splats (staged splats kpack, one byte
+  // each), added to their 2-D gradient records.  (The wave's LDS accesses
+  // execute in order; the barriers only keep the compiler from moving them.)
+  auto flush = [&](int ns, uint64_t kpack) {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+    const float4* ap = reinterpret_cast<const float4*>(s_p + col * kPixStride + 16 * kq);
+    const float4 a[4] = {ap[0], ap[1], ap[2], ap[3]};
+    // lanes 0..7 form the geometry sums of splat `lane`; lanes 8..15 hold the
+    // colour sums of splat `lane - 8`
+    const int k = (int)(kpack >> (8 * (lane & 7))) & (kStaged - 1);
+    const uint32_t ctr = S.ctr[k];
+    const bool sx = ctr & 1u, sy = ctr & 2u;
+    const float4 x = S.aux[k];  // qb, qc', dy at the quadrant's first row, 1 / opacity
+    const float qa = S.hdr[k].x;
+    const float ub = S.rows[k][sy ? 5 : 1].y;
+    const uint32_t gid = S.gid[(int)(kpack >> (8 * vslot)) & (kStaged - 1)];
+    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t], a[t].x, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t + 1], a[t].y, acc1, 0, 0, 0);
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t + 2], a[t].z, acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t + 3], a[t].w, acc1, 0, 0, 0);
+    }
+    // features 4 kq + r (lane row kq) of column `col`: q of splat col, or w
+    // of splat col - 8.  Each lane row picks its splat's centre's features,
+    // then row 0 gets them all.
+    const f32x4 acc = acc0 + acc1;
+    float gx = sx ? acc[1] : acc[0], gy = sy ? acc[3] : acc[2];  // rows 1, 2: x, y | x^2, y^2
+    float gxy = sx ? (sy ? acc[3] : acc[2]) : (sy ? acc[1] : acc[0]);  // row 3
+    const float m00 = acc[0], m10 = next_row(gx), m01 = next_row(gy);
+    const float m20 = upper_half(gx), m02 = upper_half(gy), m11 = upper_half(next_row(gxy));
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+    if (lane < 8) {
+      // u = dx - qb dy and dy at the centre
+      const float U = fmaf(-0.5f, x.x, ub + (sx ? 5.5f : 1.5f)), D = x.z + (sy ? 5.5f : 1.5f);
+      const float su = fmaf(U, m00, fmaf(-x.x, m01, m10));   // sum q u
+      const float sux = fmaf(U, m10, fmaf(-x.x, m11, m20));  // sum q u x
+      const float suy = fmaf(U, m01, fmaf(-x.x, m02, m11));  // sum q u y
+      const float suu = fmaf(U, su, fmaf(-x.x, suy, sux));   // sum q u^2
+      const float sd = fmaf(D, m00, m01);                  // sum q dy
+      const float sdd = fmaf(D, sd, fmaf(D, m01, m02));  // sum q dy^2
+      const float sud = fmaf(D, su, suy);                  // sum q u dy
+      // q = dL/de = ln2 w' dL/dw' per pixel was stored without the ln2, and
+      // e = log2(o) - qa' u^2 - qc' dy^2, u = dx - qb dy, dx = px + 1/2 - mean x
+      const float au = (2.f * kLn2) * qa * su;
+      float4* v = reinterpret_cast<float4*>(s_p + lane * kSumStride);
+      v[0] = make_float4(au,                                       // mean x
+                         fmaf((2.f * kLn2) * x.y, sd, -x.x * au),  // mean y
+                         (-kLn2 * kHalfLog2e) * suu,               // qa
+                         (2.f * kLn2) * qa * sud);                 // qb
+      *reinterpret_cast<float2*>(v + 1) =
+          make_float2((-kLn2 * kHalfLog2e) * sdd,                  // qc
+                      m00 * x.w);                                  // opacity
+    } else if (lane < 16) {
+      float* v = s_p + (lane - 8) * kSumStride + 6;
+      *reinterpret_cast<float2*>(v) = make_float2(acc[1], acc[2]);
+      v[2] = acc[3];
+    }
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+    if (lane < ns * kVals)
+      atomicAdd(grad2d + (size_t)gid * kGrad2dStride + vj, s_p[vslot * kSumStride + vj]);
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  int staged = 0;  // splats in S
+  int skip = 0;    // of them, the first `skip` lie at or past this pixel's `last`
+  int ns = 0;      // splats in the group
+  uint64_t kpack = 0;
+  // One staged splat's visit.  Lanes never branch apart: a pair a lane must
+  // not revisit (at or past its `last`, or weight below alpha_min) gets
+  // alpha = 0, which leaves T and R bitwise unchanged and yields zero
+  // gradients.
+  auto visit = [&](int k, float e, const float4& h) {
+    const bool take = k >= skip && e >= log2_tau;
+    if (!ballot(take)) return;
+    const float gw = take ? hw_exp2(e) : 0.f;
+    const float alpha = __builtin_amdgcn_fmed3f(gw, 0.f, amax);  // as the forward
+    // T before this splat, T / (1 - alpha): the hardware reciprocal's product
+    // and one correction step (its errors would add up over the walk; exact
+    // where alpha = 0).  1 - alpha >= 1 - alpha_max, far from 0.
+    const float om = 1.f - alpha, rc = __builtin_amdgcn_rcpf(om), Tr = T * rc;
+    const float Ti = fmaf(fmaf(-om, Tr, T), rc, Tr);
+    const float d = fmaf(dC2, h.w, fmaf(dC1, h.z, dC0 * h.y)) - R;
+    // no gradient flows through alpha where the alpha_max clamp binds
+    const float dal = take && gw < amax ? Ti * d : 0.f;
+    R = fmaf(alpha, d, R);
+    T = Ti;
+    float* dst = s_p + ns * kPixStride + lane;
+    dst[0] = gw * dal;
+    dst[8 * kPixStride] = alpha * Ti;
+    kpack |= (uint64_t)k << (8 * ns);
+    if (++ns == kGroup) {
+      flush(kGroup, kpack);
+      ns = 0;
+      kpack = 0;
+    }
+  };
+
+  // Batches cover positions [0, nlast) of the tile's range, last batch
+  // first.  A batch's hits are appended to the staged splats, and the walk
+  // runs when they are full, so that it and its groups stay long where few
+  // of a tile's splats reach the quadrant.  The next batch's records and the
+  // indices after it load meanwhile; loads below position 0 are clamped to
+  // it (their values are never staged).
+  int bi = (int)((nlast + kBatch - 1) / kBatch) - 1;
+  int done = 0;  // hits of batch bi already staged
+  auto pos_of = [&](int i) { return start + min((uint32_t)max(i, 0) * kBatch + lane, nlast - 1); };
+  uint32_t g_cur = values[pos_of(bi)];
+  uint32_t g_next = values[pos_of(bi - 1)];
+  SplatRec r_cur = load_splat(splats, g_cur);
+  for (;;) {
+    while (bi >= 0 && staged < kStaged) {
+      const uint32_t bs = (uint32_t)bi * kBatch;
+      const bool hit = bs + lane < nlast && reaches(r_cur, tx0, ty0, ty0 + 7);
+      const uint64_t hits = ballot(hit);
+      const int nh = __builtin_popcountll(hits);
+      const int rank = __builtin_popcountll(hits >> lane >> 1);  // back to front
+      // the first nskip hits lie at positions >= mylast
+      const int nskip = mylast <= bs ? nh
+                        : mylast - bs < (uint32_t)kBatch
+                            ? __builtin_popcountll(hits >> (mylast - bs)) : 0;
+      const int m = min(nh - done, kStaged - staged);
+      const int k = staged + rank - done;
+      if (hit && rank >= done && rank < done + m) {
+        const QuadTerms t(r_cur, tx0, ty0);
+        S.hdr[k] = make_float4(t.qa, r_cur.b.z, r_cur.b.w, r_cur.c);
+        S.aux[k] = make_float4(t.qb, t.qc, t.uy, 1.f / r_cur.b.y);
+        S.ctr[k] = (t.ux < -3.5f ? 1u : 0u) | (t.uy < -3.5f ? 2u : 0u);
+        S.gid[k] = g_cur;
+        t.rows(S.rows[k]);
+      }
+      skip += min(max(nskip - done, 0), m);
+      staged += m;
+      done += m;
+      if (done == nh) {
+        done = 0;
+        --bi;
+        g_cur = g_next;
+        r_cur = load_splat(splats, g_cur);
+        g_next = values[pos_of(bi - 1)];
+      }
+    }
+    if (staged == 0) break;
     __syncthreads();
-    // Lanes never branch apart: a pair a lane must not revisit (position at
-    // or past its `last`, or weight below alpha_min) gets alpha = 0, which
-    // leaves T, S and B bitwise unchanged and yields zero gradients.
-    // One splat's visit: the back-to-front state update and this lane's
-    // gradient terms (zero where the lane does not take the splat).  False
-    // when no lane takes it (nothing changes).
-    struct Terms {
-      float q, a, uu, r, g, b;  // dQ, dQ qa' u, dQ u^2, dL/d(r, g, b) of the pixel
-    };
-    auto visit = [&](int k, float u, float e, const float4& h, Terms& t) -> bool {
-      const bool take = S.pos[k] < mylast && e >= log2_tau;
-      if (!ballot(take)) return false;
-      const float gw = take ? hw_exp2(e) : 0.f;
-      const float alpha = __builtin_amdgcn_fmed3f(gw, 0.f, set.amax);  // as the forward
-      const float om = 1.f - alpha;
-      // T before this splat; 1 - alpha >= 1 - alpha_max, far from 0
-      const float Ti = take ? T * __builtin_amdgcn_rcpf(om) : T;
-      const float cr = h.y, cg = h.z, cb = h.w;
-      const float w = alpha * Ti;
-      const float dalpha = Ti * (dC0 * (cr - S0) + dC1 * (cg - S1) + dC2 * (cb - S2) -
-                                 B * bgdot + dA * B);
-      S0 = fmaf(alpha, cr - S0, S0);
-      S1 = fmaf(alpha, cg - S1, S1);
-      S2 = fmaf(alpha, cb - S2, S2);
-      B *= om;
-      T = Ti;
-      // weight 2^e, e = log2(o) - Q', Q' = qa' u^2 + qc' dy^2,
-      // u = dx - qb dy, dx = px + 1/2 - mean_x, dy = py + 1/2 - mean_y;
-      // no gradient flows through alpha where the alpha_max clamp binds
-      const float dal = take && gw < set.amax ? dalpha : 0.f;
-      t.q = -kLn2 * gw * dal;  // dL/dQ'
-      t.a = t.q * (h.x * u);
-      t.uu = t.q * (u * u);
-      t.r = dC0 * w;
-      t.g = dC1 * w;
-      t.b = dC2 * w;
-      return true;
-    };
-    // The 9 gradient sums of splat k over this lane's pixel row, written
-    // by the row's last lane to dst[0..8].  Per pixel, with dQ = dL/dQ':
-    //   mean x: -2 dQ qa' u      mean y: 2 dQ (qa' u qb - qc' dy)
-    //   qa': c dQ u^2            qb: -2 dQ qa' u dy
-    //   qc': c dQ dy^2           opacity: dal 2^e / o = -dQ / (ln2 o)
-    // (c = log2(e) / 2).  dy is the same for the 8 pixels of a row, so the
-    // row's 9 sums follow from the row sums of dQ, dQ qa' u and dQ u^2 and
-    // the 3 colour terms.
-    auto row_sums = [&](int k, const Terms& t, float* dst) {
-      const float sQ = oct_sum_dpp(t.q), sA = oct_sum_dpp(t.a), sU = oct_sum_dpp(t.uu);
-      const float sr = oct_sum_dpp(t.r), sg = oct_sum_dpp(t.g), sb = oct_sum_dpp(t.b);
-      if ((lane & 7) == 7) {
-        const float4 x = S.aux[k];  // qb, qc', dy at the quadrant's first row, 1 / opacity
-        const float dy = x.z + rowf;
-        *reinterpret_cast<float4*>(dst) =
-            make_float4(-2.f * sA, 2.f * (sA * x.x - (x.y * dy) * sQ), kHalfLog2e * sU,
-                        -2.f * dy * sA);
-        *reinterpret_cast<float4*>(dst + 4) =
-            make_float4(kHalfLog2e * (dy * dy) * sQ, -sQ * x.w * (1.f / kLn2), sr, sg);
-        dst[8] = sb;
-      }
-    };
-    // The 8 rows' sums added up and sent with one float-atomic instruction:
-    // lane j < 9 adds value j of splat k0, lane 12 + j value j of splat k1
-    // (when `both`).
-    auto send = [&](int k0, int k1, bool both) {
-      const int j = lane % 12;
-      if (lane < (both ? 24 : 12) && j < 9) {
-        const float v = ((s_red[0][lane] + s_red[1][lane]) + (s_red[2][lane] + s_red[3][lane])) +
-                        ((s_red[4][lane] + s_red[5][lane]) + (s_red[6][lane] + s_red[7][lane]));
-        const uint32_t gid = S.gid[lane < 12 ? k0 : k1];
-        atomicAdd(grad2d + (size_t)gid * kGrad2dStride + j, v);
-      }
-    };
-    // two staged splats per step, back to front: both LDS reads are in
-    // flight before the first one is visited; the two visits' gradients go
-    // through one LDS exchange and one atomic instruction
-    for (int k0 = nh - 1; k0 >= 0; k0 -= 2) {
-      const bool two = k0 > 0;
-      const int k1 = two ? k0 - 1 : k0;
-      const float2 q0 = S.rows[k0][row], q1 = S.rows[k1][row];
-      const float4 h0 = S.hdr[k0], h1 = S.hdr[k1];
+    // The staged splats, back to front, two per step: both LDS reads are in
+    // flight before the first one is visited (an odd last step reads a stale
+    // slot and does not visit it).
+    for (int k0 = 0; k0 < staged; k0 += 2) {
+      const float2 q0 = S.rows[k0][row], q1 = S.rows[k0 + 1][row];
+      const float4 h0 = S.hdr[k0], h1 = S.hdr[k0 + 1];
       const float u0 = q0.y + lxf, u1 = q1.y + lxf;
       const float e0 = fmaf(-h0.x, u0 * u0, q0.x);
       const float e1 = fmaf(-h1.x, u1 * u1, q1.x);
-      Terms t0, t1;
-      const bool v0 = visit(k0, u0, e0, h0, t0);
-      const bool v1 = two && visit(k1, u1, e1, h1, t1);
-      if (v0 && v1) {
-        row_sums(k0, t0, s_red[row]);
-        row_sums(k1, t1, s_red[row] + 12);
-        send(k0, k1, true);
-      } else if (v0 || v1) {
-        const int k = v0 ? k0 : k1;
-        row_sums(k, v0 ? t0 : t1, s_red[row]);
-        send(k, k, false);
-      }
+      visit(k0, e0, h0);
+      if (k0 + 1 < staged) visit(k0 + 1, e1, h1);
     }
+    if (ns > 0) flush(ns, kpack);
+    ns = 0;
+    kpack = 0;
+    __syncthreads();
+    staged = 0;
+    skip = 0;
   }
 }
 

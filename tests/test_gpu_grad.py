@@ -140,3 +140,33 @@ def test_backward_accumulate(R):
         d = np.abs(b - 2 * a).max() / scale
         print(f"{name}: max |g2 - 2 g1| / max |g1| = {d:.2e}")
         assert d <= 1e-5, (name, d)
+
+
+@pytest.mark.parametrize("n", [1, 6, 7, 8, 14, 15, 31, 32, 33, 63, 64, 65, 97, 200])
+def test_backward_group_remainders(R, orc, n):
+    """The compositing backward sums groups of 7 visited splats, from lists
+    of 32 staged ones, from batches of 64: n faint, overlapping Gaussians
+    that every quadrant of a 19x17 frame (ragged quadrants included) visits.
+    Tolerance: a gradient is a sum of at most 64 float32 terms per quadrant,
+    each from about 10 roundings of 2^-24, amplified up to 10-fold where the
+    moments about the quadrant's centre cancel, and the transmittance
+    recovered over n divisions adds n 2^-23: below 64 * 10 * 2^-24 + 200 *
+    2^-23 = 6e-5 of the gradient's norm; 1e-4."""
+    print_case(f"backward, {n} Gaussians visited by every quadrant")
+    from oracle import grad as og
+    rng = np.random.default_rng(100 + n)
+    sc, _ = S.fd_scene(seed=20 + n, n=n, size=32)
+    cam = S.pinhole_camera(S.look_at((0.0, 0.0, -3.0)), 19, 17, 60.0)
+    sc.means[:] = 0.4 * sc.means
+    sc.log_scales[:] = rng.normal(-0.9, 0.2, (n, 3))
+    sc.opacity_logits[:] = rng.normal(-3.0, 0.3, n)
+    pix = orc.all_pixels(cam)
+    ref = orc.render_pixels(orc.preprocess(sc, cam), cam, pix)
+    G = rng.standard_normal((len(pix), 4))
+    G[(ref["margin"] < 1e-4) | (ref["flags"] != 0)] = 0.0
+    _, g_ref = og.render_and_grad(sc, cam, pix, G)
+    _, g = gpu_grads(R, sc, cam, G.reshape(cam.height, cam.width, 4))
+    for nm in NAMES:
+        e = rel_l2(g[nm], g_ref[nm])
+        print(f"{nm}: rel L2 {e:.2e}")
+        assert e <= 1e-4, (nm, e)
