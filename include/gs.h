@@ -403,7 +403,9 @@ int32_t gs_sort_checked(int64_t n, const gs_splat* splats, const uint32_t* depth
  * for n Gaussians, `capacity` instances, this camera and these settings
  * (no HIP call; for tests and tools).  passes[0 .. *n_passes) in launch
  * order: the depth passes, then the tile passes (in sort mode 0 key
- * generation performs the first tile pass itself).  Each pass: its index
+ * generation performs the first tile pass itself, and up to 16,384 Gaussians
+ * one kernel, which counts each key's place, stands for the depth passes).
+ * Each pass: its index
  * (also the parity of the look-back words it reads in mode 1: half
  * pass % 2), digit width, which count bounds its keys (GS_PASS_KEYS_ALL:
  * n; _VISIBLE: counts[1]; _INSTANCES: counts[0], at most capacity), and in

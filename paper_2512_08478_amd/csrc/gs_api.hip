@@ -615,7 +615,9 @@ int32_t sort_impl(int64_t n, const gs_splat* splats, const uint32_t* depth_keys,
   if (fold_init)
     d.init = gs::sort_init_args(L, ws, tile_ranges, tiles, status_flag, counts, capacity,
                                 heavy_first ? U(L.tcls) : nullptr, db);
-  if (mode == 0)
+  if (mode == 0 && gs::rank_sort_fits(n, pd))
+    e = gs::launch_rank_sort(n, depth_keys, nullptr, 1, nullptr, d.v_out, d.init, "depth_pass", st);
+  else if (mode == 0)
     e = gs::launch_radix_sort_widths(d, widths, pd, false, "depth_pass", st);
   else
     e = gs::launch_radix_sort<uint32_t>(d, bits, pd, 0, false, "depth_pass", st);
@@ -755,9 +757,12 @@ int32_t gs_sort_pairs(int64_t n, const uint64_t* keys_in, const uint32_t* values
   char* ws = static_cast<char*>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto U = [&](size_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
-  gs::trace_mark(st, "sort_init");
-  hipError_t e = gs::launch_sort_init(L, ws, set->sort_mode, nullptr, 0, nullptr, nullptr, n, st);
-  if (e != hipSuccess) return hip_fail(e);
+  hipError_t e = hipSuccess;
+  if (set->sort_mode == 1) {  // tickets, histograms and look-back words
+    gs::trace_mark(st, "sort_init");
+    e = gs::launch_sort_init(L, ws, set->sort_mode, nullptr, 0, nullptr, nullptr, n, st);
+    if (e != hipSuccess) return hip_fail(e);
+  }
   gs::RadixArgs<uint64_t> a{};
   a.mode = set->sort_mode;
   a.n_grid = n;
@@ -800,9 +805,19 @@ int32_t gs_sort_pairs32(int64_t n, const uint32_t* keys_in, const uint32_t* valu
   char* ws = static_cast<char*>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto U = [&](size_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
-  gs::trace_mark(st, "sort_init");
-  hipError_t e = gs::launch_sort_init(L, ws, set->sort_mode, nullptr, 0, nullptr, nullptr, n, st);
-  if (e != hipSuccess) return hip_fail(e);
+  if (set->sort_mode == 0 && gs::rank_sort_fits(n, passes)) {
+    const hipError_t re = gs::launch_rank_sort(n, keys_in, values_in, 0, keys_out, values_out,
+                                               gs::SortInitK{}, "sort32_pass", st);
+    if (re != hipSuccess) return hip_fail(re);
+    gs::trace_mark(st, "");
+    return GS_OK;
+  }
+  hipError_t e = hipSuccess;
+  if (set->sort_mode == 1) {  // tickets, histograms and look-back words
+    gs::trace_mark(st, "sort_init");
+    e = gs::launch_sort_init(L, ws, set->sort_mode, nullptr, 0, nullptr, nullptr, n, st);
+    if (e != hipSuccess) return hip_fail(e);
+  }
   // a last pass without keys_out writes no keys: the other buffer of the
   // ping-pong pair stands in for keys_out
   uint32_t* kalt = U(L.dk[0]);

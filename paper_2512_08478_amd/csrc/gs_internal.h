@@ -207,6 +207,14 @@ template <typename KeyT>
 hipError_t launch_radix_sort(const RadixArgs<KeyT>& a, int bits, int passes, int pass_base,
                              bool last_keys, const char* label, hipStream_t st,
                              int first_pass = 0);
+// Sort mode 0's sort of few 32-bit keys (rank_sort_fits: instead of `passes`
+// radix passes): all bits of the keys in one kernel, stable, which also does the set-up when init.active;
+// `drop` leaves the all-ones keys out, kout may be NULL, vin NULL stands for
+// 0..n-1.
+bool rank_sort_fits(int64_t n, int passes);
+hipError_t launch_rank_sort(int64_t n, const uint32_t* kin, const uint32_t* vin, int drop,
+                            uint32_t* kout, uint32_t* vout, const SortInitK& init,
+                            const char* label, hipStream_t st);
 // Instances of the depth-sorted visible Gaussians: gathers their tile rects
 // (rects -> sorted_rects, depth order), counts tiles per slice, scans the
 // slices and writes (tile, Gaussian) pairs in depth order.

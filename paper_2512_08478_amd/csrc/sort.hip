@@ -28,6 +28,8 @@
 //      8-XCD part every look-back round trip leaves the XCD's L2, so the
 //      inclusive-prefix frontier advances one window per round trip.
 // Counts are read from device memory, so no host round trip is needed.
+#include <utility>
+
 #include "gs_device.h"
 #include "gs_internal.h"
 
@@ -526,6 +528,83 @@ __global__ __launch_bounds__(kBlock) void k_radix_pass(
         if (WRITE_KEYS) kout[g] = key;
         vout[g] = s_vals[j];
       }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- small sorts
+
+// Sort of at most kRankMaxN 32-bit keys in one launch: the place of key i is
+// the number of keys that sort before it, counted against all keys (a key
+// equal to key i counts if its index is smaller, so the sort is stable).
+// Workgroup g places the kRankKeys = 16 keys from 16 g on; its kRankWaves
+// waves each count against every kRankWaves-th block of 64 keys.  Lane (r, c)
+// of a wave's 4 rows of 16 lanes counts for key 16 g + c against the 16 keys
+// that row r holds, one per lane, which a row broadcast hands round (scalar
+// loads of the keys wait ~0.6 us each: 11 us at 4,096 keys).  With `drop` the
+// all-ones keys are not written (none of them sorts before another key).
+//
+// Bound: vector issue, 3 instructions per 64 comparisons, n^2 in all: 4,096
+// keys 5.4 us, 8,192 10 us, 16,384 27 us.  A radix pass is a chain of three
+// kernels of 3 to 5 us whatever the size, 11 us a pass: hence the limits,
+// kRankMaxN and kRankPerPass keys for each pass replaced (4,096 keys with
+// four passes: 44 us).
+constexpr int kRankWaves = 16;
+constexpr int kRankKeys = 16;
+constexpr int kRankMaxN = 16384;
+constexpr int kRankPerPass = 5120;
+
+// Calls f(key S of the row, S) for S = 0..15; kb: the key of the lane.
+template <typename F, int... S>
+__device__ __forceinline__ void row_keys(uint32_t kb, F&& f, std::integer_sequence<int, S...>) {
+  // DPP row_newbcast:S
+  (f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)kb, 0x150 + S, 0xF, 0xF, false), S), ...);
+}
+
+__global__ __launch_bounds__(kRankWaves * 64) void k_rank_sort(
+    const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t n, int drop,
+    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, SortInitK init) {
+  __shared__ uint32_t s_cnt[kRankWaves][64];
+  const int lane = lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (init.active)
+    sort_init_body(init, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+  const uint32_t i = blockIdx.x * kRankKeys + (lane & 15);
+  const uint32_t key = i < n ? kin[i] : 0u;
+  const uint32_t blocks = (n + 63) / 64;  // blocks of 64 keys
+  const uint32_t own = blockIdx.x * kRankKeys / 64;  // the one that holds the keys placed here
+  // the block's key of this lane; past the end a key that sorts before none
+  auto load = [&](uint32_t b) {
+    const uint32_t j = b * 64 + lane;
+    return j < n ? kin[j] : 0xFFFFFFFFu;
+  };
+  constexpr auto kRow = std::make_integer_sequence<int, 16>{};
+  uint32_t cnt = 0;
+  uint32_t next = load(wave);
+  for (uint32_t b = wave; b < blocks; b += kRankWaves) {
+    const uint32_t kb = next;
+    next = load(b + kRankWaves);
+    if (b < own)  // equal keys at smaller indices come first
+      row_keys(kb, [&](uint32_t k, int) { cnt += k <= key ? 1u : 0u; }, kRow);
+    else if (b > own)
+      row_keys(kb, [&](uint32_t k, int) { cnt += k < key ? 1u : 0u; }, kRow);
+    else
+      row_keys(kb, [&](uint32_t k, int s) {
+        const uint32_t j = b * 64 + (lane & ~15) + s;
+        cnt += k < key || (k == key && j < i) ? 1u : 0u;
+      }, kRow);
+  }
+  s_cnt[wave][lane] = cnt;
+  __syncthreads();
+  if (wave == 0) {
+    uint32_t r = 0;
+#pragma unroll
+    for (int w = 0; w < kRankWaves; ++w) r += s_cnt[w][lane];
+    r += shfl_u32(r, lane ^ 16);
+    r += shfl_u32(r, lane ^ 32);
+    if (lane < kRankKeys && i < n && !(drop && key == 0xFFFFFFFFu)) {
+      if (kout) kout[r] = key;
+      vout[r] = vin ? vin[i] : i;
     }
   }
 }
@@ -1287,6 +1366,20 @@ hipError_t launch_sort_init(const SortLayout& L, char* ws, int mode, uint32_t* t
   hipLaunchKernelGGL(k_sort_init, dim3(stream_grid(most, 1024)), dim3(kBlock), 0, st, I,
                      reinterpret_cast<uint32_t*>(ws + L.hist), mode == 1 ? kMaxPassTotal * 256 : 0,
                      reinterpret_cast<uint32_t*>(ws + L.lookback), lb_len);
+  return hipGetLastError();
+}
+
+bool rank_sort_fits(int64_t n, int passes) {
+  return n <= kRankMaxN && n <= (int64_t)kRankPerPass * passes;
+}
+
+hipError_t launch_rank_sort(int64_t n, const uint32_t* kin, const uint32_t* vin, int drop,
+                            uint32_t* kout, uint32_t* vout, const SortInitK& init,
+                            const char* label, hipStream_t st) {
+  if (n == 0) return hipSuccess;
+  trace_mark(st, label);
+  hipLaunchKernelGGL(k_rank_sort, dim3((int)((n + kRankKeys - 1) / kRankKeys)),
+                     dim3(kRankWaves * 64), 0, st, kin, vin, (uint32_t)n, drop, kout, vout, init);
   return hipGetLastError();
 }
 

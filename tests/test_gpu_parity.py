@@ -644,3 +644,39 @@ def test_sort_pairs32_bitexact(R, bits):
             _, vs2 = Rs.sort_pairs32(kt, torch.from_numpy(vals.view(np.int32)).cuda())
             np.testing.assert_array_equal(u32(vs2), vals[perm])
             np.testing.assert_array_equal(u32(kt), k)  # input untouched
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 4095, 16383, 16384, 16385])
+def test_small_sorts_equal_radix_passes(R, n):
+    """Around the sizes of the one-kernel sort (blocks of 64 keys, up to
+    16,384 of them): the 32-bit pair sort against NumPy's stable argsort, and
+    a frame's sorted keys, values and ranges, with tied depths and culled
+    Gaussians, against sort mode 1, which always runs radix passes."""
+    from paper_2512_08478_amd.render import GaussianParams, Renderer
+    rng = np.random.default_rng(n)
+    for kind in ("few", "ones", "random"):
+        print_case(f"small pair sort {kind} n={n}")
+        k = {"few": lambda: rng.integers(0, 3, n), "ones": lambda: np.full(n, 2**32 - 1),
+             "random": lambda: rng.integers(0, 2**32, n)}[kind]().astype(np.uint32)
+        k[rng.random(n) < 0.2] = 0xFFFFFFFF
+        perm = np.argsort(k, kind="stable").astype(np.uint32)
+        vals = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+        kt = torch.from_numpy(k.view(np.int32)).cuda()
+        ks, vs = R.sort_pairs32(kt, torch.from_numpy(vals.view(np.int32)).cuda(), want_keys=True)
+        np.testing.assert_array_equal(u32(ks), k[perm])
+        np.testing.assert_array_equal(u32(vs), vals[perm])
+        np.testing.assert_array_equal(u32(R.sort_pairs32(kt)[1]), perm)
+    print_case(f"small frame sort n={n}")
+    sc, cam = S.tiny_scene(seed=n, n=n)
+    tied = rng.random(n) < 0.5
+    sc.means[tied, 2] = rng.integers(0, 4, int(tied.sum())) * 0.25
+    sc.means[rng.random(n) < 0.2, 2] = -9.0  # behind the camera
+    p = GaussianParams.from_scene(sc)
+    got = []
+    for mode in (0, 1):
+        Rm = Renderer(dict(sort_mode=mode))
+        pre = Rm.preprocess(p, cam)
+        keys, values, ranges, flag, cap = Rm.sort(n, *pre, cam, want_keys=True)
+        got.append([u64(keys), u32(values), u32(ranges)[:2 * Rm.tiles(cam)], u32(flag), cap])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
