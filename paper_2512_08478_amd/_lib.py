@@ -8,6 +8,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import numpy as np
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgs.so")
 
@@ -268,12 +270,20 @@ def default_settings(**overrides) -> GsSettings:
 
 def make_camera(cam) -> GsCamera:
     """GsCamera from any object with viewmat (4x4), fx, fy, cx, cy, width,
-    height, znear."""
+    height, znear (a GsCamera is returned as it is)."""
+    if isinstance(cam, GsCamera):
+        return cam
     c = GsCamera()
-    vm = [float(x) for row in cam.viewmat for x in row] if hasattr(cam.viewmat[0], "__len__") \
-        else [float(x) for x in cam.viewmat]
-    for i in range(16):
-        c.viewmat[i] = vm[i]
+    vm = cam.viewmat
+    if isinstance(vm, np.ndarray) and vm.ndim <= 2:
+        vm = vm.ravel().tolist()
+    elif hasattr(vm[0], "__len__"):
+        vm = [float(x) for row in vm for x in row]
+    else:
+        vm = [float(x) for x in vm]
+    if len(vm) < 16:
+        raise IndexError("viewmat must have 16 elements")
+    c.viewmat[:] = vm[:16]
     c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
     c.width, c.height = int(cam.width), int(cam.height)
     c.znear = float(getattr(cam, "znear", 0.2))

@@ -17,11 +17,11 @@ __all__ = ["GaussianParams", "PackedParams", "Renderer", "Frame", "render", "GsR
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 @dataclass
@@ -136,6 +136,15 @@ def depth_range_bits(counts, headroom_bits=0):
     return min(32, max(1, r.bit_length()) + int(headroom_bits))
 
 
+def _grad_buffers(p, accumulate):
+    """New gradient buffers.  The backward overwrites the n Gaussians'
+    elements, unless it adds to them: only what it does not write is
+    cleared."""
+    per = (3, 3, 4, 1, 3 * (p.sh_degree + 1) ** 2)
+    return tuple(torch.empty_like(t) if not accumulate and t.numel() == p.n * k
+                 else torch.zeros_like(t) for t, k in zip(p.tensors(), per))
+
+
 class Renderer:
     """Holds settings and reusable workspaces for one device."""
 
@@ -147,14 +156,17 @@ class Renderer:
         L.load()
 
     # ------------------------------------------------------------ buffers
-    def _buf(self, name, nbytes, reuse=True):
-        nbytes = (max(int(nbytes), 256) + 255) // 256 * 256
+    def _buf(self, name, count, dtype=torch.uint8, reuse=True):
+        """At least `count` elements, in whole 256-byte units: the reused
+        buffer `name`, or a new one.  A name is always used with one dtype."""
+        unit = 256 // dtype.itemsize
+        count = (max(int(count), unit) + unit - 1) // unit * unit
         if not reuse:
-            return torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            return torch.empty(count, dtype=dtype, device=self.device)
         b = self._bufs.get(name)
-        if b is None or b.numel() < nbytes:
-            grown = (int(nbytes * 1.25) + 255) // 256 * 256
-            b = torch.empty(grown, dtype=torch.uint8, device=self.device)
+        if b is None or b.numel() < count:
+            grown = (int(count * 1.25) + unit - 1) // unit * unit
+            b = torch.empty(grown, dtype=dtype, device=self.device)
             self._bufs[name] = b
         return b
 
@@ -202,12 +214,12 @@ class Renderer:
         lib = L.load()
         c, s = L.make_camera(cam), self.settings
         n = p.n
-        splats = self._buf("splats", n * L.SPLAT_BYTES, reuse)[:n * L.SPLAT_BYTES]
-        dkeys = self._buf("depth_keys", n * 4, reuse).view(torch.int32)[:n]
-        rects = self._buf("rects", n * 8, reuse).view(torch.int32)[:2 * n]
-        counts = self._buf("counts", 16, reuse).view(torch.int32)[:4]
+        splats = self._buf("splats", n * L.SPLAT_BYTES, reuse=reuse)[:n * L.SPLAT_BYTES]
+        dkeys = self._buf("depth_keys", n, torch.int32, reuse)[:n]
+        rects = self._buf("rects", 2 * n, torch.int32, reuse)[:2 * n]
+        counts = self._buf("counts", 4, torch.int32, reuse)[:4]
         ws_bytes = lib.gs_workspace_size(L.GS_STAGE_PREPROCESS, n, 0, ctypes.byref(c), ctypes.byref(s))
-        ws = self._buf("ws_pre", ws_bytes, reuse)
+        ws = self._buf("ws_pre", ws_bytes, reuse=reuse)
         if isinstance(p, PackedParams):
             table = p.assets if p.assets is not None else [(0, n, p.model)]
             tab, _keep = L.asset_table(table)
@@ -249,11 +261,12 @@ class Renderer:
         if depth_bits is not None and int(depth_bits) != s.depth_bits:
             s = L.GsSettings.from_buffer_copy(s)
             s.depth_bits = int(depth_bits)
-        keys = self._buf("keys", capacity * 8, reuse).view(torch.int64)[:capacity] if want_keys else None
-        values = self._buf("values", capacity * 4, reuse).view(torch.int32)[:capacity]
+        keys = self._buf("keys", capacity, torch.int64, reuse)[:capacity] if want_keys else None
+        values = self._buf("values", capacity, torch.int32, reuse)[:capacity]
         # [start, end) per tile, then the compositing order of the tiles
-        ranges = self._buf("ranges", self.tiles(cam) * 12, reuse).view(torch.int32)[:3 * self.tiles(cam)]
-        flag = self._buf("flag", 4, reuse).view(torch.int32)[:1]
+        tiles = self.tiles(cam)
+        ranges = self._buf("ranges", 3 * tiles, torch.int32, reuse)[:3 * tiles]
+        flag = self._buf("flag", 1, torch.int32, reuse)[:1]
         ws_bytes = lib.gs_workspace_size(L.GS_STAGE_SORT, n, capacity, ctypes.byref(c), ctypes.byref(s))
         if ws_bytes == 0:
             raise L.GsError(L.GS_ERR_INVALID_ARGUMENT, "gs_workspace_size(sort)")
@@ -273,8 +286,8 @@ class Renderer:
         lib = L.load()
         s = self.settings
         n = int(keys.numel())
-        kout = self._buf("s32_keys", n * 4).view(torch.int32)[:n] if want_keys else None
-        vout = self._buf("s32_vals", n * 4).view(torch.int32)[:n]
+        kout = self._buf("s32_keys", n, torch.int32)[:n] if want_keys else None
+        vout = self._buf("s32_vals", n, torch.int32)[:n]
         ws_bytes = lib.gs_workspace_size(L.GS_STAGE_SORT_PAIRS, 0, n, None, ctypes.byref(s))
         ws = self._buf("ws_s32", ws_bytes)
         st = lib.gs_sort_pairs32(n, _p(keys), _p(values), key_bits, _p(kout), _p(vout),
@@ -315,6 +328,7 @@ class Renderer:
         see mesh_buffers)."""
         if mesh is not None:
             mesh = mesh_buffers(mesh, cam, self.device)
+        cam = L.make_camera(cam)
         splats, dkeys, rects, counts = self.preprocess(p, cam, reuse)
         keys, values, ranges, flag, cap = self.sort(p.n, splats, dkeys, rects, counts, cam, capacity,
                                                     reuse, want_keys, depth_bits)
@@ -331,7 +345,7 @@ class Renderer:
         c, s = L.make_camera(cam), self.settings
         n = p.n
         if out is None:
-            out = tuple(torch.zeros_like(t) for t in p.tensors())
+            out = _grad_buffers(p, accumulate)
         dL = dL_dimage.to(torch.float32).contiguous()
         ws_bytes = lib.gs_workspace_size(L.GS_STAGE_BACKWARD, n, 0, ctypes.byref(c), ctypes.byref(s))
         ws = self._buf("ws_bwd", ws_bytes)
@@ -381,7 +395,7 @@ class Renderer:
         s = self.settings
         n = p.n
         if out is None:
-            out = tuple(torch.zeros_like(t) for t in p.tensors())
+            out = _grad_buffers(p, accumulate)
         cam_arr = (L.GsCamera * len(cams))(*[L.make_camera(c) for c in cams])
         ptrs = (ctypes.c_void_p * len(grad2ds))(*[g.data_ptr() for g in grad2ds])
         assets = p.assets if p.assets is not None else [(0, n, p.model)]
