@@ -673,21 +673,29 @@ __device__ __forceinline__ uint32_t block_excl_max(uint32_t v, uint32_t* s_tmp) 
 
 constexpr int kKgWin = 2048;              // instances expanded per window
 constexpr int kKgWinItems = kKgWin / kBlock;
-// The fused keygen scatter: threads per workgroup and instances per window.
-// A slice's windows run one after another.  Up to kKgWideMaxN Gaussians
-// the slices fit on the GPU at once, and the kernel takes as long as its
-// heaviest slice (the nearest, largest Gaussians): 512 threads expand its
-// windows faster (1M frame 35.7 -> 29.4 us).  Beyond that the slices come
-// in several rounds, and 256-thread workgroups, more of which fit at once,
-// are faster (6M frame 82.9 -> 79.1 us).
+// The fused keygen cuts the depth-sorted Gaussians into slices of PART; a
+// workgroup of NT threads expands its slice's instances window by window, one
+// after another.  While all slices fit on the GPU at once the kernel lasts as
+// long as its heaviest slice (the nearest, largest Gaussians), which finer
+// slices and more threads per instance shorten, and the slices' digit counts
+// cost little to scan:
+//   up to kKgFineMaxN Gaussians  256, NT 256, windows of 1,024
+//                                (20k: histogram, scan and scatter 29.2 ->
+//                                23.2 us; 200k 35.6 -> 28.2 us)
+//   up to kKgMidMaxN             512, NT 512, windows of 2,048 (against 1,024
+//                                with 512 threads: 300k 36.7 -> 31.2 us, 1M
+//                                with 8-bit digits 62.3 -> 56.3 us)
+//   beyond                       1,024, NT 256: the slices come in several
+//                                rounds anyway, and their scan would grow
+//                                (6M: 146 us; with slices of 512, 161 us).
+// The histogram walks each rect's tile rows in one thread; its workgroup has
+// a thread per Gaussian, which spreads a slice's large rects.
+constexpr int kKgFinePart = 256, kKgFineThreads = 256, kKgFineWin = 1024;
+constexpr int64_t kKgFineMaxN = 262144;
+constexpr int kKgMidPart = 512, kKgMidThreads = 512;
+constexpr int64_t kKgMidMaxN = 2000000;
 constexpr int kKgScatThreads = 256;
-constexpr int kKgScatWideThreads = 512;
 constexpr int kKgScatWin = 2048;
-constexpr int64_t kKgWideMaxN = 2000000;
-// The rect histogram walks each rect's tile rows in one thread; a wider
-// workgroup spreads a slice's large rects over more threads (6M frame
-// 72.4 -> 70.8 us, 500k 11.8 -> 10.5 us against 256 threads).
-constexpr int kKgHistThreads = 1024;
 
 // Instances in depth order: slice p of the depth-sorted visible list starts
 // at kg_prefix[p] (scanned slice counts) and writes (tile id, Gaussian
@@ -787,60 +795,51 @@ __global__ __launch_bounds__(kBlock) void k_kg_write(const uint32_t* __restrict_
 
 // ---------------------------------------------------------------- keygen + first tile pass
 
-// First-tile-digit histogram of each 1024-Gaussian slice of the depth-sorted
-// visible list, written partition-major (table[slice * NB + d]), with the
-// rect gather of k_kg_count.  The tiles of one row of a rect have
-// consecutive ids, so their digits are consecutive residues mod NB: each
-// row adds one over a circular range of digits, which a difference array
-// in LDS takes as two increments (four across the wrap), and each whole
-// turn of NB tiles adds one to every digit.
-template <int BITS, int NT>
-__global__ __launch_bounds__(NT) void k_kg_hist(uint32_t n, const uint32_t* __restrict__ vis_count,
-                                                    const uint32_t* __restrict__ sorted_idx,
-                                                    const uint2* __restrict__ rects,
-                                                    uint2* __restrict__ sorted_rects,
-                                                    int tiles_x, uint32_t* __restrict__ table) {
-  constexpr int NB = 1 << BITS;
-  constexpr int KI = kKgPart / NT;  // slice Gaussians per thread
+// First-tile-digit histogram of each slice of PART Gaussians of the
+// depth-sorted visible list, written partition-major (table[slice * NB + d]),
+// with the rect gather of k_kg_count, one Gaussian per thread.  The tiles of
+// one row of a rect have consecutive ids, so their digits are consecutive
+// residues mod NB: each row adds one over a circular range of digits, which
+// a difference array in LDS takes as two increments (four across the wrap),
+// and each whole turn of NB tiles adds one to every digit.
+template <int BITS, int PART>
+__global__ __launch_bounds__(PART) void k_kg_hist(uint32_t n, const uint32_t* __restrict__ vis_count,
+                                                  const uint32_t* __restrict__ sorted_idx,
+                                                  const uint2* __restrict__ rects,
+                                                  uint2* __restrict__ sorted_rects, int tiles_x,
+                                                  uint32_t* __restrict__ table) {
+  constexpr int NB = 1 << BITS, NT = PART;
+  static_assert(NT >= NB, "a thread per digit");
   __shared__ int s_diff[NB + 1];
   __shared__ uint32_t s_tmp[NT / 64];
   __shared__ uint32_t s_turns;
   const int t = threadIdx.x;
   const uint32_t nvis = *vis_count;
-  const uint32_t base = blockIdx.x * kKgPart;
+  const uint32_t base = blockIdx.x * PART;
   if (base >= nvis) return;
   for (int d = t; d <= NB; d += NT) s_diff[d] = 0;
   if (t == 0) s_turns = 0;
-  // branch-free loads (positions past the end read the last Gaussian and
-  // are ignored), so that all four gathers are in flight together
-  uint32_t g[KI];
-  uint2 r[KI];
-#pragma unroll
-  for (int j = 0; j < KI; ++j) g[j] = sorted_idx[min(base + j * NT + t, nvis - 1)];
-#pragma unroll
-  for (int j = 0; j < KI; ++j) r[j] = rects[min(g[j], n - 1)];  // (indices are < n)
+  // a position past the end reads the last Gaussian and is ignored
+  const uint32_t p = base + t;
+  const uint2 r = rects[min(sorted_idx[min(p, nvis - 1)], n - 1)];  // (indices are < n)
   __syncthreads();
   uint32_t turns = 0;
-#pragma unroll
-  for (int j = 0; j < KI; ++j) {
-    const uint32_t p = base + j * NT + t;
-    if (p < nvis) {
-      sorted_rects[p] = r[j];
-      const uint32_t tx0 = r[j].x & 0xFFFFu, ty0 = r[j].x >> 16;
-      const uint32_t tx1 = r[j].y & 0xFFFFu, ty1 = r[j].y >> 16;
-      const uint32_t w = tx1 - tx0 + 1;
-      const uint32_t full = w >> BITS, rem = w & (NB - 1);
-      turns += full * (ty1 - ty0 + 1);
-      if (rem) {
-        for (uint32_t ty = ty0; ty <= ty1; ++ty) {
-          const uint32_t a = (ty * (uint32_t)tiles_x + tx0) & (NB - 1), e = a + rem;
-          atomicAdd(&s_diff[a], 1);
-          if (e <= NB) {
-            atomicAdd(&s_diff[e], -1);
-          } else {
-            atomicAdd(&s_diff[0], 1);
-            atomicAdd(&s_diff[e - NB], -1);
-          }
+  if (p < nvis) {
+    sorted_rects[p] = r;
+    const uint32_t tx0 = r.x & 0xFFFFu, ty0 = r.x >> 16;
+    const uint32_t tx1 = r.y & 0xFFFFu, ty1 = r.y >> 16;
+    const uint32_t w = tx1 - tx0 + 1;
+    const uint32_t full = w >> BITS, rem = w & (NB - 1);
+    turns = full * (ty1 - ty0 + 1);
+    if (rem) {
+      for (uint32_t ty = ty0; ty <= ty1; ++ty) {
+        const uint32_t a = (ty * (uint32_t)tiles_x + tx0) & (NB - 1), e = a + rem;
+        atomicAdd(&s_diff[a], 1);
+        if (e <= NB) {
+          atomicAdd(&s_diff[e], -1);
+        } else {
+          atomicAdd(&s_diff[0], 1);
+          atomicAdd(&s_diff[e - NB], -1);
         }
       }
     }
@@ -856,7 +855,7 @@ __global__ __launch_bounds__(NT) void k_kg_hist(uint32_t n, const uint32_t* __re
 
 // Key generation fused with the first radix pass over the tile keys.  Each
 // slice's instances (depth order, then row-major within a rect) are
-// expanded in windows of 2048 as in k_kg_write, ranked within the window by
+// expanded in windows of WIN as in k_kg_write, ranked within the window by
 // their first tile digit (ballot matching, stable), staged in digit order
 // and written at the digit's running offset: its global start (scanned
 // digit totals), plus its count in the earlier slices (scanned table),
@@ -864,7 +863,7 @@ __global__ __launch_bounds__(NT) void k_kg_hist(uint32_t n, const uint32_t* __re
 // no key list written and read back in between.  Positions at or past
 // `cap` are skipped (capacity overflow); every position below it still
 // receives exactly one pair.
-template <int BITS, int NT, int WIN>
+template <int BITS, int NT, int WIN, int PART>
 __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ sorted_idx,
                                                        const uint32_t* __restrict__ vis_count,
                                                        const uint2* __restrict__ sorted_rects,
@@ -877,10 +876,10 @@ __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ 
   constexpr int NB = 1 << BITS;
   constexpr int NW = NT / 64;
   constexpr int IT = WIN / NT;       // window positions per thread
-  constexpr int KI = kKgPart / NT;   // slice Gaussians per thread
-  static_assert(NT >= (1 << BITS) && kKgPart % NT == 0 && WIN % NT == 0, "shape");
-  __shared__ uint32_t s_off[kKgPart];
-  __shared__ uint32_t s_lo[kKgPart], s_hi[kKgPart], s_g[kKgPart];
+  constexpr int KI = PART / NT;   // slice Gaussians per thread
+  static_assert(NT >= (1 << BITS) && PART % NT == 0 && WIN % NT == 0, "shape");
+  __shared__ uint32_t s_off[PART];
+  __shared__ uint32_t s_lo[PART], s_hi[PART], s_g[PART];
   __shared__ uint32_t s_own[WIN];  // window owners, then the staged keys
   __shared__ uint32_t s_val[WIN];
   __shared__ uint32_t s_whist[NW][NB];
@@ -888,10 +887,10 @@ __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ 
   __shared__ uint32_t s_tmp[NW], s_sc[NW];
   const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
   const uint32_t nvis = *vis_count, cap = *inst_count;
-  const uint32_t nsl = (nvis + kKgPart - 1) / kKgPart;
+  const uint32_t nsl = (nvis + PART - 1) / PART;
   if (blockIdx.x >= nsl) return;
   const uint32_t slice = blockIdx.x;
-  const uint32_t base = slice * kKgPart;
+  const uint32_t base = slice * PART;
   // every load of the prologue is issued before the first is used
   // (branch-free: positions past the end read the last Gaussian)
   const uint32_t gcount = t < NB ? totals[t] : 0u;
@@ -1300,7 +1299,11 @@ SortLayout sort_layout(int64_t n, int64_t capacity, int tiles) {
   L.hist = take((size_t)kMaxPassTotal * 256 * 4);
   L.tickets = take((size_t)kMaxPassTotal * 4);
   L.lookback = take((size_t)2 * L.parts * 256 * 4);
-  L.table = take((size_t)L.rs_parts * kMaxDigits * 4);
+  // rows of the radix partitions (up to 512 digits) or of the keygen slices
+  // (up to 256)
+  const size_t kg_rows = nn <= kKgFineMaxN ? (size_t)((nn + kKgFinePart - 1) / kKgFinePart) : 0;
+  const size_t rs_words = (size_t)L.rs_parts * kMaxDigits;
+  L.table = take((rs_words > kg_rows * 256 ? rs_words : kg_rows * 256) * 4);
   L.totals = take(kMaxDigits * 4);
   L.kg_counts = take((size_t)L.kg_parts * 4);
   L.count = take(4);
@@ -1466,27 +1469,33 @@ hipError_t launch_keygen(int64_t n, const uint32_t* sorted_idx, const uint32_t* 
 }
 
 namespace {
-template <int BITS>
-void kg_fused_t(int64_t n, int parts, const uint32_t* sorted_idx, const uint32_t* vis_count,
+template <int BITS, int PART, int NT, int WIN>
+void kg_fused_t(int64_t n, const uint32_t* sorted_idx, const uint32_t* vis_count,
                 const uint2* rects, uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
                 uint32_t* table, uint32_t* totals, uint32_t* tkeys, uint32_t* tvals,
                 hipStream_t st) {
   constexpr int NB = 1 << BITS;
+  const int parts = (int)((n + PART - 1) / PART);
   trace_mark(st, "kg_hist");
-  hipLaunchKernelGGL((k_kg_hist<BITS, kKgHistThreads>), dim3(parts), dim3(kKgHistThreads), 0, st,
+  hipLaunchKernelGGL((k_kg_hist<BITS, PART>), dim3(parts), dim3(PART), 0, st,
                      (uint32_t)n, vis_count, sorted_idx, rects, sorted_rects, tiles_x, table);
   trace_mark(st, "kg_scan");
-  hipLaunchKernelGGL((k_col_scan<NB, kKgPart>), dim3(NB / 4), dim3(kBlock), 0, st, table,
-                     vis_count, (int64_t)0, totals);
+  hipLaunchKernelGGL((k_col_scan<NB, PART>), dim3(NB / 4), dim3(kBlock), 0, st, table, vis_count,
+                     (int64_t)0, totals);
   trace_mark(st, "keygen");
-  if (n <= kKgWideMaxN)
-    hipLaunchKernelGGL((k_kg_scatter<BITS, kKgScatWideThreads, kKgScatWin>), dim3(parts),
-                       dim3(kKgScatWideThreads), 0, st, sorted_idx, vis_count, sorted_rects,
-                       tiles_x, inst_count, table, totals, tkeys, tvals);
-  else
-    hipLaunchKernelGGL((k_kg_scatter<BITS, kKgScatThreads, kKgScatWin>), dim3(parts),
-                       dim3(kKgScatThreads), 0, st, sorted_idx, vis_count, sorted_rects,
-                       tiles_x, inst_count, table, totals, tkeys, tvals);
+  hipLaunchKernelGGL((k_kg_scatter<BITS, NT, WIN, PART>), dim3(parts), dim3(NT), 0, st, sorted_idx,
+                     vis_count, sorted_rects, tiles_x, inst_count, table, totals, tkeys, tvals);
+}
+
+template <int BITS>
+void kg_fused(int64_t n, const uint32_t* sorted_idx, const uint32_t* vis_count, const uint2* rects,
+              uint2* sorted_rects, int tiles_x, const uint32_t* inst_count, uint32_t* table,
+              uint32_t* totals, uint32_t* tkeys, uint32_t* tvals, hipStream_t st) {
+#define GS_KG(PART, NT, WIN) kg_fused_t<BITS, PART, NT, WIN>(n, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, tkeys, tvals, st)
+  if (n <= kKgFineMaxN) GS_KG(kKgFinePart, kKgFineThreads, kKgFineWin);
+  else if (n <= kKgMidMaxN) GS_KG(kKgMidPart, kKgMidThreads, kKgScatWin);
+  else GS_KG(kKgPart, kKgScatThreads, kKgScatWin);
+#undef GS_KG
 }
 }  // namespace
 
@@ -1495,16 +1504,14 @@ hipError_t launch_keygen_fused(int64_t n, int bits, const uint32_t* sorted_idx,
                                uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
                                uint32_t* table, uint32_t* totals, uint32_t* tkeys,
                                uint32_t* tvals, hipStream_t st) {
-  const int parts = (int)((n + kKgPart - 1) / kKgPart);
-  if (parts == 0) return hipSuccess;
+  if (n == 0) return hipSuccess;
+#define GS_KF(B) kg_fused<B>(n, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, tkeys, tvals, st)
   switch (bits) {
-    case 6: kg_fused_t<6>(n, parts, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count,
-                          table, totals, tkeys, tvals, st); break;
-    case 7: kg_fused_t<7>(n, parts, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count,
-                          table, totals, tkeys, tvals, st); break;
-    default: kg_fused_t<8>(n, parts, sorted_idx, vis_count, rects, sorted_rects, tiles_x,
-                           inst_count, table, totals, tkeys, tvals, st); break;
+    case 6: GS_KF(6); break;
+    case 7: GS_KF(7); break;
+    default: GS_KF(8); break;
   }
+#undef GS_KF
   return hipGetLastError();
 }
 

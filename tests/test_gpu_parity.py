@@ -680,3 +680,28 @@ def test_small_sorts_equal_radix_passes(R, n):
         got.append([u64(keys), u32(values), u32(ranges)[:2 * Rm.tiles(cam)], u32(flag), cap])
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("n", [255, 256, 257, 511, 513, 262144, 262145, 2_000_001])
+def test_keygen_slices_equal_mode_1(n, bits):
+    """The fused keygen in slices of 256 (up to 262,144 Gaussians), 512 (up to
+    2,000,000) and 1,024 Gaussians, at slice remainders and on both sides of
+    each limit: sorted keys, values and ranges equal those of sort mode 1,
+    whose keygen is a separate kernel.  Some splats cover the whole grid of
+    1,024 tiles (several turns of the digits per rect)."""
+    from paper_2512_08478_amd.render import GaussianParams, Renderer
+    print_case(f"keygen slices n={n} bits={bits}")
+    rng = np.random.default_rng(n)
+    sc, cam = S.tiny_scene(seed=3, n=n)
+    sc.log_scales[rng.choice(n, min(n, 40), replace=False)] = 1.0
+    sc.means[rng.random(n) < 0.2, 2] = -9.0
+    p = GaussianParams.from_scene(sc)
+    got = []
+    for mode in (0, 1):
+        Rm = Renderer(dict(sort_mode=mode, radix_bits=bits, tile_w=8, tile_h=8))
+        pre = Rm.preprocess(p, cam)
+        keys, values, ranges, flag, cap = Rm.sort(n, *pre, cam, want_keys=True)
+        got.append([u64(keys), u32(values), u32(ranges)[:2 * Rm.tiles(cam)], u32(flag), cap])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
