@@ -641,8 +641,10 @@ int32_t sort_impl(int64_t n, const gs_splat* splats, const uint32_t* depth_keys,
     // key generation writes the output of the first tile pass directly
     uint32_t* fk = pt > 1 ? U(L.tk[0]) : U(L.tkf);
     uint32_t* fv = pt > 1 ? U(L.tv[0]) : values;
-    e = gs::launch_keygen_fused(n, bits, U(L.dv[0]), counts + 1, rects, drect, tiles_x, count,
-                                U(L.table), U(L.totals), fk, fv, st);
+    e = gs::launch_keygen_fused(n, capacity, bits, U(L.dv[0]), counts + 1, rects, drect, tiles_x,
+                                count, U(L.table), U(L.totals), U(L.tickets), U(L.kg_counts),
+                                reinterpret_cast<uint2*>(ws + L.kg_list), L.kg_list_max, fk, fv,
+                                st);
     if (e != hipSuccess) return hip_fail(e);
     t.kin = fk;
     t.vin = fv;

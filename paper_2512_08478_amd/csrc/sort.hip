@@ -677,23 +677,33 @@ constexpr int kKgWinItems = kKgWin / kBlock;
 // workgroup of NT threads expands its slice's instances window by window, one
 // after another.  While all slices fit on the GPU at once the kernel lasts as
 // long as its heaviest slice (the nearest, largest Gaussians), which finer
-// slices and more threads per instance shorten, and the slices' digit counts
-// cost little to scan:
+// slices and more threads per instance shorten; but each slice costs a
+// prologue and a row of digit counts to scan.  Histogram, scan and scatter of
+// 16x16-tile frames at 1920x1080 (~3.4 instances per Gaussian) and at 66x49
+// (~0.9), 8-bit digits, us (slices of 1,024 with 512 threads in brackets):
 //   up to kKgFineMaxN Gaussians  256, NT 256, windows of 1,024
-//                                (20k: histogram, scan and scatter 29.2 ->
-//                                23.2 us; 200k 35.6 -> 28.2 us)
-//   up to kKgMidMaxN             512, NT 512, windows of 2,048 (against 1,024
-//                                with 512 threads: 300k 36.7 -> 31.2 us, 1M
-//                                with 8-bit digits 62.3 -> 56.3 us)
+//                                (60k: 30.9 (45.6) and 21.0 (22.3), 250k:
+//                                36.4 (51.1) and 25.3 (23.7))
+//   up to kKgMidMaxN, and up to  512, NT 512, windows of 2,048
+//   kKgMidDenseMaxN where there  (400k: 41.5 (55.2) and 29.8 (28.8), 900k:
+//   is room for two instances    54.2 (62.4) and 43.8 (37.2), 1.1M: 61.4
+//   per Gaussian                 (66.2) and 48.7 (40.0))
+//   up to kKgWideMaxN            1,024, NT 512 (1.9M: 86.6 and 58.8; with
+//                                slices of 512, 93.4 and 71.3)
 //   beyond                       1,024, NT 256: the slices come in several
-//                                rounds anyway, and their scan would grow
-//                                (6M: 146 us; with slices of 512, 161 us).
+//                                rounds anyway (6M: 146 us; with slices of
+//                                512, 161 us).
 // The histogram walks each rect's tile rows in one thread; its workgroup has
 // a thread per Gaussian, which spreads a slice's large rects.
 constexpr int kKgFinePart = 256, kKgFineThreads = 256, kKgFineWin = 1024;
 constexpr int64_t kKgFineMaxN = 262144;
 constexpr int kKgMidPart = 512, kKgMidThreads = 512;
-constexpr int64_t kKgMidMaxN = 2000000;
+constexpr int64_t kKgMidMaxN = 600000, kKgMidDenseMaxN = 1300000;
+constexpr int64_t kKgWideMaxN = 2000000;
+int kg_part(int64_t n, int64_t capacity) {
+  if (n <= kKgFineMaxN) return kKgFinePart;
+  return n <= kKgMidMaxN || (n <= kKgMidDenseMaxN && capacity >= 2 * n) ? kKgMidPart : kKgPart;
+}
 constexpr int kKgScatThreads = 256;
 constexpr int kKgScatWin = 2048;
 
@@ -795,62 +805,99 @@ __global__ __launch_bounds__(kBlock) void k_kg_write(const uint32_t* __restrict_
 
 // ---------------------------------------------------------------- keygen + first tile pass
 
+// The keygen's heavy slices: a slice with more than kKgChunk instances is
+// expanded in chunks of that many, the first by its own workgroup, the others
+// by one workgroup each.  The histogram lists these: *count of them wanted
+// (cleared by the set-up), list[e] = (slice, chunk) of the first list_max,
+// base[slice] = the place of a heavy slice's chunk 1.  (Their order in the
+// list is of no account: each chunk's output places follow from the counts.)
+struct KgHeavyK {
+  uint32_t* count;
+  uint32_t* base;
+  uint2* list;
+  uint32_t list_max;
+};
+constexpr uint32_t kKgChunk = 16384;
+
+// The first tile digits of `len` consecutive tile ids from `first` on, added
+// to the difference array diff[NB + 1]; returns the whole turns of the digits,
+// which add one to every digit each.
+template <int NB>
+__device__ __forceinline__ uint32_t add_digit_run(int* diff, uint32_t first, uint32_t len) {
+  const uint32_t rem = len & (NB - 1);
+  if (rem) {
+    const uint32_t a = first & (NB - 1), e = a + rem;
+    atomicAdd(&diff[a], 1);
+    if (e <= NB) {
+      atomicAdd(&diff[e], -1);
+    } else {
+      atomicAdd(&diff[0], 1);
+      atomicAdd(&diff[e - NB], -1);
+    }
+  }
+  return len / NB;
+}
+
 // First-tile-digit histogram of each slice of PART Gaussians of the
 // depth-sorted visible list, written partition-major (table[slice * NB + d]),
 // with the rect gather of k_kg_count, one Gaussian per thread.  The tiles of
 // one row of a rect have consecutive ids, so their digits are consecutive
 // residues mod NB: each row adds one over a circular range of digits, which
 // a difference array in LDS takes as two increments (four across the wrap),
-// and each whole turn of NB tiles adds one to every digit.
+// and each whole turn of NB tiles adds one to every digit.  A heavy
+// slice's further chunks go to the list.
 template <int BITS, int PART>
 __global__ __launch_bounds__(PART) void k_kg_hist(uint32_t n, const uint32_t* __restrict__ vis_count,
                                                   const uint32_t* __restrict__ sorted_idx,
                                                   const uint2* __restrict__ rects,
                                                   uint2* __restrict__ sorted_rects, int tiles_x,
-                                                  uint32_t* __restrict__ table) {
+                                                  uint32_t* __restrict__ table,
+                                                  KgHeavyK heavy) {
   constexpr int NB = 1 << BITS, NT = PART;
   static_assert(NT >= NB, "a thread per digit");
   __shared__ int s_diff[NB + 1];
   __shared__ uint32_t s_tmp[NT / 64];
-  __shared__ uint32_t s_turns;
+  __shared__ uint32_t s_turns, s_inst;
   const int t = threadIdx.x;
   const uint32_t nvis = *vis_count;
   const uint32_t base = blockIdx.x * PART;
   if (base >= nvis) return;
   for (int d = t; d <= NB; d += NT) s_diff[d] = 0;
-  if (t == 0) s_turns = 0;
+  if (t == 0) s_turns = s_inst = 0;
   // a position past the end reads the last Gaussian and is ignored
   const uint32_t p = base + t;
   const uint2 r = rects[min(sorted_idx[min(p, nvis - 1)], n - 1)];  // (indices are < n)
   __syncthreads();
-  uint32_t turns = 0;
+  uint32_t turns = 0, inst = 0;
   if (p < nvis) {
     sorted_rects[p] = r;
     const uint32_t tx0 = r.x & 0xFFFFu, ty0 = r.x >> 16;
     const uint32_t tx1 = r.y & 0xFFFFu, ty1 = r.y >> 16;
-    const uint32_t w = tx1 - tx0 + 1;
-    const uint32_t full = w >> BITS, rem = w & (NB - 1);
-    turns = full * (ty1 - ty0 + 1);
-    if (rem) {
-      for (uint32_t ty = ty0; ty <= ty1; ++ty) {
-        const uint32_t a = (ty * (uint32_t)tiles_x + tx0) & (NB - 1), e = a + rem;
-        atomicAdd(&s_diff[a], 1);
-        if (e <= NB) {
-          atomicAdd(&s_diff[e], -1);
-        } else {
-          atomicAdd(&s_diff[0], 1);
-          atomicAdd(&s_diff[e - NB], -1);
-        }
-      }
-    }
+    for (uint32_t ty = ty0; ty <= ty1; ++ty)
+      turns += add_digit_run<NB>(s_diff, ty * (uint32_t)tiles_x + tx0, tx1 - tx0 + 1);
+    inst = rect_tiles(r.x, r.y);
   }
   turns = wave_sum_u32(turns);
-  if (lane_id() == 0 && turns) atomicAdd(&s_turns, turns);
+  inst = wave_sum_u32(inst);
+  if (lane_id() == 0) {
+    if (turns) atomicAdd(&s_turns, turns);
+    atomicAdd(&s_inst, inst);
+  }
   __syncthreads();
   const uint32_t v = t < NB ? (uint32_t)s_diff[t] : 0u;
   uint32_t tot;
   const uint32_t incl = block_excl_scan<NT>(v, s_tmp, &tot) + v;
   if (t < NB) table[(size_t)blockIdx.x * NB + t] = incl + s_turns;
+  const uint32_t slice_inst = s_inst;
+  if (slice_inst > kKgChunk) {
+    __syncthreads();
+    const uint32_t more = (slice_inst - 1) / kKgChunk;
+    if (t == 0) heavy.base[blockIdx.x] = s_turns = atomicAdd(heavy.count, more);
+    __syncthreads();
+    const uint32_t e0 = s_turns;
+    for (uint32_t k = t; k < more && e0 + k < heavy.list_max; k += NT)
+      heavy.list[e0 + k] = make_uint2(blockIdx.x, k + 1);
+  }
 }
 
 // Key generation fused with the first radix pass over the tile keys.  Each
@@ -863,21 +910,32 @@ __global__ __launch_bounds__(PART) void k_kg_hist(uint32_t n, const uint32_t* __
 // no key list written and read back in between.  Positions at or past
 // `cap` are skipped (capacity overflow); every position below it still
 // receives exactly one pair.
+//
+// Workgroup b < slices_grid expands slice b's first kKgChunk instances (all,
+// but for heavy slices), the workgroups after them one further chunk of the
+// list each; where the list is full (only with more instances than the
+// capacity) the chunk before the missing ones runs to its slice's end.  A
+// chunk that is not its slice's first counts the digits of the instances
+// before it from the rects, as the histogram does.  With the eye among the
+// Gaussians a few slices hold most instances: 6M Gaussians with a cluster at
+// the near plane (18M instances) 11,500 -> 282 us.
 template <int BITS, int NT, int WIN, int PART>
 __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ sorted_idx,
-                                                       const uint32_t* __restrict__ vis_count,
-                                                       const uint2* __restrict__ sorted_rects,
-                                                       int tiles_x,
-                                                       const uint32_t* __restrict__ inst_count,
-                                                       const uint32_t* __restrict__ table,
-                                                       const uint32_t* __restrict__ totals,
-                                                       uint32_t* __restrict__ tkeys,
-                                                       uint32_t* __restrict__ tvals) {
+                                                   const uint32_t* __restrict__ vis_count,
+                                                   const uint2* __restrict__ sorted_rects,
+                                                   int tiles_x,
+                                                   const uint32_t* __restrict__ inst_count,
+                                                   const uint32_t* __restrict__ table,
+                                                   const uint32_t* __restrict__ totals,
+                                                   KgHeavyK heavy, uint32_t slices_grid,
+                                                   uint32_t* __restrict__ tkeys,
+                                                   uint32_t* __restrict__ tvals) {
   constexpr int NB = 1 << BITS;
   constexpr int NW = NT / 64;
   constexpr int IT = WIN / NT;       // window positions per thread
   constexpr int KI = PART / NT;   // slice Gaussians per thread
-  static_assert(NT >= (1 << BITS) && PART % NT == 0 && WIN % NT == 0, "shape");
+  static_assert(NT >= (1 << BITS) && PART % NT == 0 && WIN % NT == 0 &&
+                    kKgChunk % WIN == 0, "shape");
   __shared__ uint32_t s_off[PART];
   __shared__ uint32_t s_lo[PART], s_hi[PART], s_g[PART];
   __shared__ uint32_t s_own[WIN];  // window owners, then the staged keys
@@ -885,11 +943,21 @@ __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ 
   __shared__ uint32_t s_whist[NW][NB];
   __shared__ uint32_t s_local[NB], s_scat[NB];
   __shared__ uint32_t s_tmp[NW], s_sc[NW];
+  __shared__ int s_diff[NB + 1];
+  __shared__ uint32_t s_turns;
   const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
   const uint32_t nvis = *vis_count, cap = *inst_count;
   const uint32_t nsl = (nvis + PART - 1) / PART;
-  if (blockIdx.x >= nsl) return;
-  const uint32_t slice = blockIdx.x;
+  uint32_t slice = blockIdx.x, chunk = 0;
+  if (slice < slices_grid) {
+    if (slice >= nsl) return;
+  } else {
+    const uint32_t e = slice - slices_grid;
+    if (e >= *heavy.count) return;
+    const uint2 sc = heavy.list[e];
+    slice = sc.x;
+    chunk = sc.y;
+  }
   const uint32_t base = slice * PART;
   // every load of the prologue is issued before the first is used
   // (branch-free: positions past the end read the last Gaussian)
@@ -923,16 +991,42 @@ __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ 
     s_off[t * KI + j] = run;
     run += cnt[j];
   }
-  // running write base of digit t: its global start plus its count in the
-  // earlier slices
+  // the running write base of digit t: its global start plus its count in
+  // the earlier slices, and in the slice's earlier chunks
   uint32_t gb = 0;
   {
     uint32_t all;
     const uint32_t gstart = block_excl_scan<NT>(gcount, s_sc, &all);
     if (t < NB) gb = gstart + tprefix;
   }
+  const uint32_t first = chunk * kKgChunk;
+  // (the next chunk is missing where the list is full)
+  const uint32_t last = btot - first <= kKgChunk || heavy.base[slice] + chunk >= heavy.list_max
+                            ? btot : first + kKgChunk;
+  if (chunk > 0) {
+    for (int d = t; d <= NB; d += NT) s_diff[d] = 0;
+    if (t == 0) s_turns = 0;
+    __syncthreads();
+    uint32_t turns = 0;
+    for (int li = t; li < PART && base + li < nvis && s_off[li] < first; li += NT) {
+      const uint32_t lo = s_lo[li], hi = s_hi[li];
+      const uint32_t m = min(rect_tiles(lo, hi), first - s_off[li]);  // instances before
+      if (m == 0) continue;
+      const uint32_t tx0 = lo & 0xFFFFu, w = (hi & 0xFFFFu) - tx0 + 1, rows = m / w;
+      uint32_t id = (lo >> 16) * (uint32_t)tiles_x + tx0;
+      for (uint32_t r = 0; r < rows; ++r, id += (uint32_t)tiles_x)
+        turns += add_digit_run<NB>(s_diff, id, w);
+      turns += add_digit_run<NB>(s_diff, id, m - rows * w);
+    }
+    turns = wave_sum_u32(turns);
+    if (lane == 0 && turns) atomicAdd(&s_turns, turns);
+    __syncthreads();
+    const uint32_t v = t < NB ? (uint32_t)s_diff[t] : 0u;
+    uint32_t all;
+    gb += block_excl_scan<NT>(v, s_sc, &all) + v + s_turns;
+  }
   const uint64_t lt = lanemask_lt();
-  for (uint32_t w0 = 0; w0 < btot; w0 += WIN) {
+  for (uint32_t w0 = first; w0 < last; w0 += WIN) {
 #pragma unroll
     for (int k = 0; k < IT; ++k) s_own[t * IT + k] = 0;
     for (int b = t; b < NW * NB; b += NT) (&s_whist[0][0])[b] = 0;
@@ -967,7 +1061,7 @@ __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ 
       const uint32_t kk = w0 + q;
       key[i] = 0;
       val[i] = 0;
-      if (kk < btot) {
+      if (kk < last) {
         const uint32_t li = s_own[q] - 1;
         const uint32_t local = kk - s_off[li];
         const uint32_t rl = s_lo[li], rh = s_hi[li];
@@ -1283,7 +1377,6 @@ SortLayout sort_layout(int64_t n, int64_t capacity, int tiles) {
   const int64_t big = nn > cap ? nn : cap;
   L.parts = (int)((big + kSortPart - 1) / kSortPart);
   L.rs_parts = (int)((big + kBlock * 4 - 1) / (kBlock * 4));
-  L.kg_parts = (int)((nn + kKgPart - 1) / kKgPart);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -1301,11 +1394,15 @@ SortLayout sort_layout(int64_t n, int64_t capacity, int tiles) {
   L.lookback = take((size_t)2 * L.parts * 256 * 4);
   // rows of the radix partitions (up to 512 digits) or of the keygen slices
   // (up to 256)
-  const size_t kg_rows = nn <= kKgFineMaxN ? (size_t)((nn + kKgFinePart - 1) / kKgFinePart) : 0;
+  const int part = kg_part(nn, cap);
+  const size_t kg_rows = (size_t)((nn + part - 1) / part);
   const size_t rs_words = (size_t)L.rs_parts * kMaxDigits;
   L.table = take((rs_words > kg_rows * 256 ? rs_words : kg_rows * 256) * 4);
   L.totals = take(kMaxDigits * 4);
-  L.kg_counts = take((size_t)L.kg_parts * 4);
+  L.kg_counts = take(kg_rows * 4);
+  // the further chunks of at most `cap` instances
+  L.kg_list_max = (uint32_t)(cap / kKgChunk + 1);
+  L.kg_list = take((size_t)L.kg_list_max * 8);
   L.count = take(4);
   L.tcls = take((size_t)kTileClasses * 4);
   L.tseg = take((size_t)kTileClasses * (tiles > 0 ? tiles : 1) * 4);
@@ -1318,7 +1415,6 @@ SortLayout pairs_layout(int64_t n) {
   const int64_t nn = n > 0 ? n : 1;
   L.parts = (int)((nn + kSortPart - 1) / kSortPart);
   L.rs_parts = (int)((nn + kBlock * 4 - 1) / (kBlock * 4));
-  L.kg_parts = 0;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -1333,7 +1429,8 @@ SortLayout pairs_layout(int64_t n) {
   L.lookback = take((size_t)2 * L.parts * 256 * 4);
   L.table = take((size_t)L.rs_parts * kMaxDigits * 4);
   L.totals = take(kMaxDigits * 4);
-  L.kg_counts = 0;
+  L.kg_counts = L.kg_list = 0;
+  L.kg_list_max = 0;
   L.count = take(4);
   L.bytes = o;
   return L;
@@ -1472,40 +1569,47 @@ namespace {
 template <int BITS, int PART, int NT, int WIN>
 void kg_fused_t(int64_t n, const uint32_t* sorted_idx, const uint32_t* vis_count,
                 const uint2* rects, uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
-                uint32_t* table, uint32_t* totals, uint32_t* tkeys, uint32_t* tvals,
-                hipStream_t st) {
+                uint32_t* table, uint32_t* totals, const KgHeavyK& heavy, uint32_t* tkeys,
+                uint32_t* tvals, hipStream_t st) {
   constexpr int NB = 1 << BITS;
   const int parts = (int)((n + PART - 1) / PART);
   trace_mark(st, "kg_hist");
   hipLaunchKernelGGL((k_kg_hist<BITS, PART>), dim3(parts), dim3(PART), 0, st,
-                     (uint32_t)n, vis_count, sorted_idx, rects, sorted_rects, tiles_x, table);
+                     (uint32_t)n, vis_count, sorted_idx, rects, sorted_rects, tiles_x, table,
+                     heavy);
   trace_mark(st, "kg_scan");
   hipLaunchKernelGGL((k_col_scan<NB, PART>), dim3(NB / 4), dim3(kBlock), 0, st, table, vis_count,
                      (int64_t)0, totals);
   trace_mark(st, "keygen");
-  hipLaunchKernelGGL((k_kg_scatter<BITS, NT, WIN, PART>), dim3(parts), dim3(NT), 0, st, sorted_idx,
-                     vis_count, sorted_rects, tiles_x, inst_count, table, totals, tkeys, tvals);
+  hipLaunchKernelGGL((k_kg_scatter<BITS, NT, WIN, PART>), dim3(parts + heavy.list_max), dim3(NT), 0,
+                     st, sorted_idx, vis_count, sorted_rects, tiles_x, inst_count, table, totals,
+                     heavy, (uint32_t)parts, tkeys, tvals);
 }
 
 template <int BITS>
-void kg_fused(int64_t n, const uint32_t* sorted_idx, const uint32_t* vis_count, const uint2* rects,
-              uint2* sorted_rects, int tiles_x, const uint32_t* inst_count, uint32_t* table,
-              uint32_t* totals, uint32_t* tkeys, uint32_t* tvals, hipStream_t st) {
-#define GS_KG(PART, NT, WIN) kg_fused_t<BITS, PART, NT, WIN>(n, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, tkeys, tvals, st)
-  if (n <= kKgFineMaxN) GS_KG(kKgFinePart, kKgFineThreads, kKgFineWin);
-  else if (n <= kKgMidMaxN) GS_KG(kKgMidPart, kKgMidThreads, kKgScatWin);
+void kg_fused(int64_t n, int64_t capacity, const uint32_t* sorted_idx, const uint32_t* vis_count,
+              const uint2* rects, uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
+              uint32_t* table, uint32_t* totals, const KgHeavyK& heavy, uint32_t* tkeys, uint32_t* tvals,
+              hipStream_t st) {
+#define GS_KG(PART, NT, WIN) kg_fused_t<BITS, PART, NT, WIN>(n, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, heavy, tkeys, tvals, st)
+  const int part = kg_part(n, capacity);
+  if (part == kKgFinePart) GS_KG(kKgFinePart, kKgFineThreads, kKgFineWin);
+  else if (part == kKgMidPart) GS_KG(kKgMidPart, kKgMidThreads, kKgScatWin);
+  else if (n <= kKgWideMaxN) GS_KG(kKgPart, kKgMidThreads, kKgScatWin);
   else GS_KG(kKgPart, kKgScatThreads, kKgScatWin);
 #undef GS_KG
 }
 }  // namespace
 
-hipError_t launch_keygen_fused(int64_t n, int bits, const uint32_t* sorted_idx,
+hipError_t launch_keygen_fused(int64_t n, int64_t capacity, int bits, const uint32_t* sorted_idx,
                                const uint32_t* vis_count, const uint2* rects,
                                uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
-                               uint32_t* table, uint32_t* totals, uint32_t* tkeys,
-                               uint32_t* tvals, hipStream_t st) {
+                               uint32_t* table, uint32_t* totals, uint32_t* heavy_count,
+                               uint32_t* kg_counts, uint2* kg_list, uint32_t kg_list_max,
+                               uint32_t* tkeys, uint32_t* tvals, hipStream_t st) {
+  const KgHeavyK heavy{heavy_count, kg_counts, kg_list, kg_list_max};
   if (n == 0) return hipSuccess;
-#define GS_KF(B) kg_fused<B>(n, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, tkeys, tvals, st)
+#define GS_KF(B) kg_fused<B>(n, capacity, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, heavy, tkeys, tvals, st)
   switch (bits) {
     case 6: GS_KF(6); break;
     case 7: GS_KF(7); break;

@@ -705,3 +705,52 @@ def test_keygen_slices_equal_mode_1(n, bits):
         got.append([u64(keys), u32(values), u32(ranges)[:2 * Rm.tiles(cam)], u32(flag), cap])
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("n,short", [(200, False), (200, True), (700, False), (700, True),
+                                     (270_000, False), (1_400_000, False), (2_000_001, False)])
+def test_heavy_keygen_slices(n, bits, short):
+    """Slices of more than 16,384 instances are expanded in chunks by several
+    workgroups: 160 splats in front of the others, each over a part of the
+    1,024 tiles or over all of them, at the head of a slice and across two
+    slices, with the full capacity (equal to sort mode 1) and with one that
+    leaves the list of chunks short (the instances that the first tile-digit
+    pass places below it are kept, in order)."""
+    from paper_2512_08478_amd.render import GaussianParams, Renderer
+    print_case(f"heavy keygen slices n={n} bits={bits} short={short}")
+    sc, cam = S.tiny_scene(seed=5, n=n)
+    rng = np.random.default_rng(n)
+    heavy = np.arange(160)
+    sc.means[heavy] = rng.uniform(-0.6, 0.6, (160, 3)) + np.array([0.0, 0.0, -1.8])
+    sc.log_scales[heavy] = rng.uniform(-1.5, 1.0, (160, 1))
+    p = GaussianParams.from_scene(sc)
+    over = dict(radix_bits=bits, tile_w=8, tile_h=8)
+    R1 = Renderer(dict(over, sort_mode=1))
+    R0 = Renderer(dict(over, sort_mode=0))
+    pre = R1.preprocess(p, cam)
+    tot = int(u32(pre[3])[0])
+    assert tot > 4 * 16384
+    if not short:
+        got = []
+        for Rm in (R0, R1):
+            keys, values, ranges, flag, cap = Rm.sort(n, *pre, cam, want_keys=True)
+            got.append([u64(keys), u32(values), u32(ranges)[:2 * Rm.tiles(cam)], u32(flag), cap])
+        for a, b in zip(*got):
+            np.testing.assert_array_equal(a, b)
+        return
+    cap = 20_000  # two entries in the list
+    gen = generation_order(u32(pre[1]), u32(pre[2]), 32)
+    kept = gen[np.argsort(gen[:, 0] & ((1 << bits) - 1), kind="stable")][:cap]
+    kept = kept[np.argsort(kept[:, 0], kind="stable")]
+    _, values, ranges, flag, _ = R0.sort(n, *pre, cam, capacity=cap)
+    torch.cuda.synchronize()
+    assert int(u32(flag)[0]) & 1 == 1
+    rg = u32(ranges)[:2 * R0.tiles(cam)].reshape(-1, 2).astype(np.int64)
+    vals = u32(values)[:cap]
+    np.testing.assert_array_equal(vals, kept[:, 1])
+    first = np.searchsorted(kept[:, 0], np.arange(len(rg)))
+    last = np.searchsorted(kept[:, 0], np.arange(len(rg)), side="right")
+    full = last > first
+    np.testing.assert_array_equal(rg[full], np.stack([first, last], 1)[full])
+    assert np.all(rg[~full, 1] <= rg[~full, 0])
