@@ -1090,7 +1090,7 @@ BatchLayout batch_layout(const gs_batch* b, int64_t capacity) {
   L.recs = take((size_t)vn * sizeof(gs_splat));
   L.dkeys = take((size_t)vn * 4);
   L.rects = take((size_t)vn * 8);
-  L.partial = take((size_t)b->V * b->pre.block0[b->A] * 16);
+  L.partial = take((size_t)gs::preprocess_views_slots(b->V, b->pre.block0[b->A], b->deg) * 16);
   L.counts = take(16);
   L.T = take((size_t)b->pixels * 4);
   L.last = take((size_t)b->pixels * 4);
@@ -1161,8 +1161,8 @@ hipError_t batch_preprocess(const gs_batch* b, char* ws, hipStream_t st) {
       reinterpret_cast<uint4*>(ws + L.partial), st);
   if (e == hipSuccess)
     e = gs::launch_count_finalize(reinterpret_cast<const uint4*>(ws + L.partial),
-                                  b->V * b->pre.block0[b->A], reinterpret_cast<uint32_t*>(ws + L.counts),
-                                  st);
+                                  gs::preprocess_views_slots(b->V, b->pre.block0[b->A], b->deg),
+                                  reinterpret_cast<uint32_t*>(ws + L.counts), st);
   return e;
 }
 

@@ -9,7 +9,7 @@
 namespace gs {
 
 constexpr int kBlock = 256;          // threads per block for streaming kernels
-constexpr int kViewsPerBlock = 16;   // views a batch preprocess workgroup projects in turn
+constexpr int kViewsPerBlock = 16;   // views a batch preprocess workgroup projects in turn, at most
 constexpr int kSortItems = 16;       // keys per thread in a radix pass
 constexpr int kSortPart = kBlock * kSortItems;  // keys per partition (4096)
 constexpr int kMaxPassTotal = 32;    // radix passes per call (depth + tile, or 64-bit)
@@ -156,8 +156,9 @@ int preprocess_blocks(int64_t n);
 // Projection of n Gaussians; per-block (instances, visible, smallest and
 // largest visible depth key) partials go to partial[0 .. preprocess_blocks(n)).
 // Every view x asset of a batch in one launch (k_preprocess_views); cams
-// (device) holds n_views * n_assets cameras, view-major.  Partials: n_views *
-// B.block0[n_assets] slots.
+// (device) holds n_views * n_assets cameras, view-major.  Partials:
+// preprocess_views_slots(n_views, B.block0[n_assets], degree) slots.
+int preprocess_views_slots(int n_views, int blocks, int degree);
 hipError_t launch_preprocess_views(const BatchPreK& B, int n_views, const float* means,
                                    const float* log_scales, const float* quats,
                                    const float* logits, const float* sh, int degree,

@@ -142,15 +142,15 @@ __device__ __forceinline__ void place_mean(float p0, float p1, float p2, const C
   t[2] = fma((double)cam.V[8], w0, fma((double)cam.V[9], w1, fma((double)cam.V[10], w2, (double)cam.V[11])));
 }
 
-// Each workgroup's (instances, visible) totals into its slot of `partial`
-// (summed later by k_count_finalize); tiles = this thread's tile count.
-__device__ __forceinline__ void block_counts(uint32_t tiles, uint32_t dkey, uint4* __restrict__ partial) {
+// Each workgroup's instances, visible Gaussians and depth key range into its
+// slot of `partial` (summed later by k_count_finalize), from each thread's
+// (tiles, visible, smallest and largest key: all ones and 0 if it has none).
+__device__ __forceinline__ void block_counts(uint32_t tiles, uint32_t visible, uint32_t kmin,
+                                             uint32_t kmax, uint4* __restrict__ partial) {
   __shared__ uint32_t s_vis[kBlock / 64], s_til[kBlock / 64], s_min[kBlock / 64], s_max[kBlock / 64];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const uint32_t wv = (uint32_t)__builtin_popcountll(ballot(tiles > 0));
+  const uint32_t wv = wave_sum_u32(visible);
   const uint32_t wt = wave_sum_u32(tiles);
-  // depth key range of the visible Gaussians (culled keys are all ones)
-  uint32_t kmin = dkey, kmax = tiles > 0 ? dkey : 0u;
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     kmin = min(kmin, shfl_u32(kmin, lane ^ d));

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_packed(
     dst[1] = r1;
     dst[2] = r2;
   }
-  block_counts(tiles, dkey, partial);
+  block_counts(tiles, tiles > 0 ? 1u : 0u, dkey, tiles > 0 ? dkey : 0u, partial);
 }
 
 // Linear blend skinning of pre-packed canonical Gaussians (the avatar

@@ -18,57 +18,75 @@
 namespace gs {
 namespace {
 
+// rgb = sum_k sh_k Y_k + 1/2 from an SH row of 16-byte vectors.
+template <int DEG>
+__device__ __forceinline__ void row_colour(const float4* rowp, const float* Y, float* rgb) {
+  constexpr int K = (DEG + 1) * (DEG + 1);
+  float v[K * 3];
+#pragma unroll
+  for (int j = 0; j < K * 3 / 4; ++j) {
+    const float4 f = rowp[j];
+    v[4 * j] = f.x; v[4 * j + 1] = f.y; v[4 * j + 2] = f.z; v[4 * j + 3] = f.w;
+  }
+  float acc[3] = {0.5f, 0.5f, 0.5f};
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    acc[0] = fmaf(v[3 * k], Y[k], acc[0]);
+    acc[1] = fmaf(v[3 * k + 1], Y[k], acc[1]);
+    acc[2] = fmaf(v[3 * k + 2], Y[k], acc[2]);
+  }
+  rgb[0] = acc[0]; rgb[1] = acc[1]; rgb[2] = acc[2];
+}
+
 // rgb = sum_k sh_k Y_k + 1/2 for Gaussian i (before the clamp at 0).
 template <int DEG>
 __device__ __forceinline__ void sh_colour(const float* __restrict__ sh, int i, const float* Y,
                                           float* rgb) {
   constexpr int K = (DEG + 1) * (DEG + 1);
-  float acc[3] = {0.5f, 0.5f, 0.5f};
   if constexpr (DEG == 1 || DEG == 3) {
     // rows are 48 or 192 bytes: 16-byte aligned float4 loads
-    const float4* row = reinterpret_cast<const float4*>(sh + (size_t)i * K * 3);
-    float v[K * 3];
-#pragma unroll
-    for (int j = 0; j < K * 3 / 4; ++j) {
-      const float4 f = row[j];
-      v[4 * j] = f.x; v[4 * j + 1] = f.y; v[4 * j + 2] = f.z; v[4 * j + 3] = f.w;
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      acc[0] = fmaf(v[3 * k], Y[k], acc[0]);
-      acc[1] = fmaf(v[3 * k + 1], Y[k], acc[1]);
-      acc[2] = fmaf(v[3 * k + 2], Y[k], acc[2]);
-    }
+    row_colour<DEG>(reinterpret_cast<const float4*>(sh + (size_t)i * K * 3), Y, rgb);
   } else {
     const float* row = sh + (size_t)i * K * 3;
+    float acc[3] = {0.5f, 0.5f, 0.5f};
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       acc[0] = fmaf(row[3 * k], Y[k], acc[0]);
       acc[1] = fmaf(row[3 * k + 1], Y[k], acc[1]);
       acc[2] = fmaf(row[3 * k + 2], Y[k], acc[2]);
     }
+    rgb[0] = acc[0]; rgb[1] = acc[1]; rgb[2] = acc[2];
   }
-  rgb[0] = acc[0]; rgb[1] = acc[1]; rgb[2] = acc[2];
 }
 
-// Eq. 1 and the colour for Gaussian i; fills its record r0..r2 and returns
-// the number of tiles it touches (0 if culled).  With STAGED_SH the colour
-// is left to the caller, which gets the SH view direction in dir[].
-template <int DEG, bool STAGED_SH>
-__device__ __forceinline__ uint32_t project_one(
-    int i, const float* __restrict__ means, const float* __restrict__ log_scales,
-    const float4* __restrict__ quats, const float* __restrict__ logits,
-    const float* __restrict__ sh, const CamK& cam, const SetK& set, float4& r0, float4& r1,
-    float4& r2, uint2& trect, float* dir) {
-  const float4 q = quats[i];
-  const float lg = logits[i];
+// The scales and the rotation of a Gaussian: what of its covariance does not
+// depend on the view.
+struct Shape {
+  float s[3], R[9];
+  __device__ __forceinline__ Shape(const float4& q, float qn2, float l0, float l1, float l2) {
+    s[0] = expf(l0); s[1] = expf(l1); s[2] = expf(l2);
+    const float inv = 1.f / sqrtf(qn2);
+    const float qw = q.x * inv, qx = q.y * inv, qy = q.z * inv, qz = q.w * inv;
+    R[0] = 1.f - 2.f * (qy * qy + qz * qz); R[1] = 2.f * (qx * qy - qw * qz); R[2] = 2.f * (qx * qz + qw * qy);
+    R[3] = 2.f * (qx * qy + qw * qz); R[4] = 1.f - 2.f * (qx * qx + qz * qz); R[5] = 2.f * (qy * qz - qw * qx);
+    R[6] = 2.f * (qx * qz - qw * qy); R[7] = 2.f * (qy * qz + qw * qx); R[8] = 1.f - 2.f * (qx * qx + qy * qy);
+  }
+};
+
+// Eq. 1 for one Gaussian with mean p, opacity o, squared quaternion length
+// qn2 and the Shape that shape() gives (asked for only if the Gaussian lies
+// in front of the camera); fills its record r0..r2 but for the colour and
+// returns the number of tiles it touches (0 if culled) and the SH view
+// direction in dir[].
+template <class ShapeFn>
+__device__ __forceinline__ uint32_t project(float p0, float p1, float p2, float o, float qn2,
+                                            ShapeFn shape, const CamK& cam, const SetK& set,
+                                            float4& r0, float4& r1, float4& r2, uint2& trect,
+                                            float* dir) {
   float w[3];
   double t[3];
-  place_mean(means[3 * i], means[3 * i + 1], means[3 * i + 2], cam, w, t);
+  place_mean(p0, p1, p2, cam, w, t);
   const float tx = (float)t[0], ty = (float)t[1], tz = (float)t[2];
-
-  const float o = 1.f / (1.f + expf(-lg));
-  const float qn2 = q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
 
   r0 = make_float4(0.f, 0.f, 0.f, 0.f);
   r1 = r0;
@@ -83,23 +101,17 @@ __device__ __forceinline__ uint32_t project_one(
   if (ok) {
     // Sigma = R diag(s^2) R^T; with N = T3 R diag(s), camera-space
     // covariance is N N^T and S = J N N^T J^T + eps I = M M^T + eps I.
-    const float s0 = expf(log_scales[3 * i]), s1 = expf(log_scales[3 * i + 1]),
-                s2 = expf(log_scales[3 * i + 2]);
-    const float inv = 1.f / sqrtf(qn2);
-    const float qw = q.x * inv, qx = q.y * inv, qy = q.z * inv, qz = q.w * inv;
-    float R[9];
-    R[0] = 1.f - 2.f * (qy * qy + qz * qz); R[1] = 2.f * (qx * qy - qw * qz); R[2] = 2.f * (qx * qz + qw * qy);
-    R[3] = 2.f * (qx * qy + qw * qz); R[4] = 1.f - 2.f * (qx * qx + qz * qz); R[5] = 2.f * (qy * qz - qw * qx);
-    R[6] = 2.f * (qx * qz - qw * qy); R[7] = 2.f * (qy * qz + qw * qx); R[8] = 1.f - 2.f * (qx * qx + qy * qy);
+    const Shape g = shape();
     float N[9];
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
       for (int c = 0; c < 3; ++c)
-        N[3 * r + c] = fmaf(cam.T3[3 * r], R[c], fmaf(cam.T3[3 * r + 1], R[3 + c], cam.T3[3 * r + 2] * R[6 + c]));
-    N[0] *= s0; N[3] *= s0; N[6] *= s0;
-    N[1] *= s1; N[4] *= s1; N[7] *= s1;
-    N[2] *= s2; N[5] *= s2; N[8] *= s2;
+        N[3 * r + c] = fmaf(cam.T3[3 * r], g.R[c], fmaf(cam.T3[3 * r + 1], g.R[3 + c], cam.T3[3 * r + 2] * g.R[6 + c]));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      N[c] *= g.s[c]; N[3 + c] *= g.s[c]; N[6 + c] *= g.s[c];
+    }
     // Jacobian of the perspective division at t (x/z, y/z clamped)
     const float iz = 1.f / tz;
     const float xt = fminf(cam.limx, fmaxf(-cam.limx, tx * iz));
@@ -124,20 +136,23 @@ __device__ __forceinline__ uint32_t project_one(
                     set.eps2d * (aa + cc) + set.eps2d * set.eps2d;
     tiles = footprint(t, iz, w[0], w[1], w[2], aa + set.eps2d, b, cc + set.eps2d, D, o, cam,
                       set, r0, r1, rect_lo, rect_hi, trect, dir);
-    if (!STAGED_SH && tiles) {
-      float Y[16];
-      sh_basis<DEG>(dir[0], dir[1], dir[2], Y);
-      float rgb[3];
-      sh_colour<DEG>(sh, i, Y, rgb);
-      r1.z = fmaxf(rgb[0], 0.f);
-      r1.w = fmaxf(rgb[1], 0.f);
-      r2.x = fmaxf(rgb[2], 0.f);
-    }
   }
   r2.y = tz;
   r2.z = __uint_as_float(rect_lo);
   r2.w = __uint_as_float(rect_hi);
   return tiles;
+}
+
+__device__ __forceinline__ float opacity_of(float logit) { return 1.f / (1.f + expf(-logit)); }
+__device__ __forceinline__ float norm2(const float4& q) {
+  return q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
+}
+
+// The colour into the record.
+__device__ __forceinline__ void set_colour(const float* rgb, float4& r1, float4& r2) {
+  r1.z = fmaxf(rgb[0], 0.f);
+  r1.w = fmaxf(rgb[1], 0.f);
+  r2.x = fmaxf(rgb[2], 0.f);
 }
 
 // SH rows per wave staged through LDS at a time (half a wave's Gaussians).
@@ -170,8 +185,18 @@ __device__ __forceinline__ void preprocess_block(
   uint2 trect;
   float dir[3] = {0.f, 0.f, 0.f};
   if (i < n) {
-    tiles = project_one<DEG, STAGED>(i, means, log_scales, quats, logits, sh, cam, set, r0, r1,
-                                     r2, trect, dir);
+    const float4 q = quats[i];
+    const float qn2 = norm2(q);
+    tiles = project(means[3 * i], means[3 * i + 1], means[3 * i + 2], opacity_of(logits[i]), qn2,
+                    [&] { return Shape(q, qn2, log_scales[3 * i], log_scales[3 * i + 1],
+                                       log_scales[3 * i + 2]); },
+                    cam, set, r0, r1, r2, trect, dir);
+    if (!STAGED && tiles) {
+      float Y[16], rgb[3];
+      sh_basis<DEG>(dir[0], dir[1], dir[2], Y);
+      sh_colour<DEG>(sh, i, Y, rgb);
+      set_colour(rgb, r1, r2);
+    }
     dkey = tiles ? __float_as_uint(r2.y) : 0xFFFFFFFFu;
     depth_keys[i] = dkey;
     rects[i] = trect;
@@ -202,25 +227,10 @@ __device__ __forceinline__ void preprocess_block(
         if (f < kShRows * F4) buf[f] = pre[h][k];
       }
       if (tiles > 0 && lane / kShRows == h) {
-        const float4* rowp = buf + (lane - h * kShRows) * F4;
-        float v[K * 3];
-#pragma unroll
-        for (int j = 0; j < F4; ++j) {
-          const float4 q = rowp[j];
-          v[4 * j] = q.x; v[4 * j + 1] = q.y; v[4 * j + 2] = q.z; v[4 * j + 3] = q.w;
-        }
-        float Y[16];
+        float Y[16], rgb[3];
         sh_basis<DEG>(dir[0], dir[1], dir[2], Y);
-        float acc[3] = {0.5f, 0.5f, 0.5f};
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          acc[0] = fmaf(v[3 * k], Y[k], acc[0]);
-          acc[1] = fmaf(v[3 * k + 1], Y[k], acc[1]);
-          acc[2] = fmaf(v[3 * k + 2], Y[k], acc[2]);
-        }
-        r1.z = fmaxf(acc[0], 0.f);
-        r1.w = fmaxf(acc[1], 0.f);
-        r2.x = fmaxf(acc[2], 0.f);
+        row_colour<DEG>(buf + (lane - h * kShRows) * F4, Y, rgb);
+        set_colour(rgb, r1, r2);
       }
     }
   }
@@ -230,7 +240,7 @@ __device__ __forceinline__ void preprocess_block(
     dst[1] = r1;
     dst[2] = r2;
   }
-  block_counts(tiles, dkey, partial);
+  block_counts(tiles, tiles > 0 ? 1u : 0u, dkey, tiles > 0 ? dkey : 0u, partial);
 }
 
 template <int DEG>
@@ -245,45 +255,87 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(
 
 // Every view of a batch and every asset in one launch: blockIdx.x runs over
 // the assets' blocks (asset a owns blocks [B.block0[a], B.block0[a + 1])),
-// blockIdx.y over chunks of kViewsPerBlock views, which the workgroup
-// projects one after the other: its Gaussians' inputs come from HBM for the
-// first view and from the cache for the others, instead of once per view.
-// View v's records, depth keys and tile rects start at v * B.n; view v's
-// partial counts of workgroup b go to slot v * B.block0[n_assets] + b.
-// cams[v * n_assets + a] places asset a in view v.
+// blockIdx.y over chunks of `per` views, which the workgroup projects one
+// after the other.  View v's records, depth keys and tile rects
+// start at v * B.n; the workgroup's counts over its views go to partial slot
+// blockIdx.y * blocks + blockIdx.x.  cams[v * n_assets + a] places asset a in
+// view v.
+//
+// Each wave keeps its Gaussians' SH rows in LDS for all its views (degrees 1
+// and 3, whose rows are whole 16-byte vectors; an odd row stride in vectors,
+// so the lanes' row reads meet no bank conflicts) and what of the projection
+// does not depend on the view in registers.  Bound: the records' writes and
+// vector issue.  Measured against a projection per view from the
+// cached inputs (SH staged for each view, 1,015 vector instructions per wave
+// and view): 32 views of 4.5M, degree 3, 5.34 -> 2.76 ms (10.6 GB, 3.8 TB/s),
+// 12 views of 200k 130 -> 69 us, 24 views of 20k 77 -> 28 us; the sum of the
+// partial counts, one per workgroup instead of one per view, 199 -> 19 us.
 template <int DEG>
-// 4 waves per SIMD (124 VGPRs, no spill once the inputs are not kept live
-// across the views; 194 VGPRs and 2 waves otherwise): 5.7 -> 5.4 ms per
-// batch of 32 views x 4.5 M Gaussians.
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_preprocess_views(
-    BatchPreK B, int n_views, const float* __restrict__ means,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_preprocess_views(
+    BatchPreK B, int n_views, int per, const float* __restrict__ means,
     const float* __restrict__ log_scales, const float4* __restrict__ quats,
     const float* __restrict__ logits, const float* __restrict__ sh,
     const CamK* __restrict__ cams, SetK set, gs_splat* __restrict__ splats,
     uint32_t* __restrict__ depth_keys, uint2* __restrict__ rects, uint4* __restrict__ partial) {
-  constexpr int K3 = (DEG + 1) * (DEG + 1) * 3;
-  const int b = blockIdx.x;
+  constexpr int K = (DEG + 1) * (DEG + 1);
+  constexpr bool STAGED = DEG == 1 || DEG == 3;
+  constexpr int F4 = STAGED ? K * 3 / 4 : 1;  // float4 per SH row
+  constexpr int STRIDE = F4 | 1;
+  __shared__ float4 s_sh[STAGED ? kBlock * STRIDE : 1];
+  const int b = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
   int a = 0;
   while (a + 1 < B.n_assets && B.block0[a + 1] <= b) ++a;
   const int64_t o = B.offset[a];
-  const int v0 = blockIdx.y * kViewsPerBlock;
-  const int v1 = min(n_views, v0 + kViewsPerBlock);
-  for (int v = v0; v < v1; ++v) {
-    const int64_t vo = (int64_t)v * B.n + o;
-    // opaque input pointers: each view reads its inputs again (from the
-    // cache) instead of the compiler keeping them, and all that derives
-    // from them, live across the views
-    const float* m = means + 3 * o;
-    const float* ls = log_scales + 3 * o;
-    const float4* qt = quats + o;
-    const float* lg = logits + o;
-    asm volatile("" : "+s"(m), "+s"(ls), "+s"(qt), "+s"(lg));
-    preprocess_block<DEG>(b - B.block0[a], B.count[a], m, ls, qt, lg, sh + K3 * o,
-                          cams[v * B.n_assets + a], set,
-                          splats + vo, depth_keys + vo, rects + vo,
-                          partial + (size_t)v * B.block0[B.n_assets]);  // slot blockIdx.x
-    __syncthreads();  // the next view reuses the LDS of this one
+  const int n = B.count[a], i0 = (b - B.block0[a]) * kBlock, i = i0 + threadIdx.x;
+  const int v0 = blockIdx.y * per;
+  const int v1 = min(n_views, v0 + per);
+  means += 3 * o; log_scales += 3 * o; quats += o; logits += o; sh += (int64_t)K * 3 * o;
+  float4* rows = s_sh + (STAGED ? wave * 64 * STRIDE : 0);
+  if constexpr (STAGED) {
+    const float4* src = reinterpret_cast<const float4*>(sh) + (size_t)(i0 + wave * 64) * F4;
+    const int len = min(64, max(0, n - (i0 + wave * 64))) * F4;
+#pragma unroll
+    for (int k = 0; k < F4; ++k) {
+      const int f = lane + 64 * k;
+      if (f < len) rows[f / F4 * STRIDE + f % F4] = src[f];
+    }
   }
+  uint32_t tot = 0, vis = 0, kmin = 0xFFFFFFFFu, kmax = 0;
+  if (i < n) {
+    const float p0 = means[3 * i], p1 = means[3 * i + 1], p2 = means[3 * i + 2];
+    const float4 q = quats[i];
+    const float qn2 = norm2(q), op = opacity_of(logits[i]);
+    const Shape g(q, qn2, log_scales[3 * i], log_scales[3 * i + 1], log_scales[3 * i + 2]);
+    for (int v = v0; v < v1; ++v) {
+      const int64_t at = (int64_t)v * B.n + o + i;
+      float4 r0, r1, r2;
+      uint2 trect;
+      float dir[3];
+      const uint32_t tiles = project(p0, p1, p2, op, qn2, [&] { return g; },
+                                     cams[v * B.n_assets + a], set, r0, r1, r2, trect, dir);
+      if (tiles) {
+        float Y[16], rgb[3];
+        sh_basis<DEG>(dir[0], dir[1], dir[2], Y);
+        if constexpr (STAGED)
+          row_colour<DEG>(rows + lane * STRIDE, Y, rgb);
+        else
+          sh_colour<DEG>(sh, i, Y, rgb);
+        set_colour(rgb, r1, r2);
+        const uint32_t dkey = __float_as_uint(r2.y);
+        tot += tiles;
+        vis += 1;
+        kmin = min(kmin, dkey);
+        kmax = max(kmax, dkey);
+      }
+      depth_keys[at] = tiles ? __float_as_uint(r2.y) : 0xFFFFFFFFu;
+      rects[at] = trect;
+      float4* dst = reinterpret_cast<float4*>(splats + at);
+      dst[0] = r0;
+      dst[1] = r1;
+      dst[2] = r2;
+    }
+  }
+  block_counts(tot, vis, kmin, kmax, partial + (size_t)blockIdx.y * gridDim.x);
 }
 
 #pragma float_control(pop)
@@ -729,6 +781,32 @@ hipError_t launch_preprocess(int n, const float* means, const float* log_scales,
   return hipGetLastError();
 }
 
+// Views per workgroup.  Reading a Gaussian's inputs costs a workgroup about
+// as much as two views, and 256 CUs hold 3 workgroups each (5 below degree
+// 3): the split, of at most kViewsPerBlock views, with the least rounds times
+// cost (24 views of 5k 53 us 16 at a time, 17-20 us so split; 12 views of 200k
+// 83 and 69-73 us).
+static int views_per_block(int n_views, int blocks, int degree) {
+  const int64_t resident = 256 * (degree == 3 ? 3 : 5);
+  int best = 1;
+  int64_t cost = INT64_MAX;
+  for (int per = n_views < kViewsPerBlock ? n_views : kViewsPerBlock; per >= 1; --per) {
+    const int64_t chunks = (n_views + per - 1) / per;
+    const int64_t c = (blocks * chunks + resident - 1) / resident * (per + 2);
+    if (c < cost) {
+      cost = c;
+      best = per;
+    }
+  }
+  return best;
+}
+
+int preprocess_views_slots(int n_views, int blocks, int degree) {
+  if (n_views < 1) return 0;
+  const int per = views_per_block(n_views, blocks, degree);
+  return (n_views + per - 1) / per * blocks;
+}
+
 hipError_t launch_preprocess_views(const BatchPreK& B, int n_views, const float* means,
                                    const float* log_scales, const float* quats,
                                    const float* logits, const float* sh, int degree,
@@ -739,8 +817,9 @@ hipError_t launch_preprocess_views(const BatchPreK& B, int n_views, const float*
   if (blocks > 0 && n_views > 0) {
     trace_mark(st, "preprocess_views");
     const float4* q4 = reinterpret_cast<const float4*>(quats);
-    const int chunks = (n_views + kViewsPerBlock - 1) / kViewsPerBlock;
-#define GS_PREV(D) hipLaunchKernelGGL(k_preprocess_views<D>, dim3(blocks, chunks), dim3(kBlock), 0, st, B, n_views, means, log_scales, q4, logits, sh, cams, set, splats, depth_keys, reinterpret_cast<uint2*>(tile_rects), partial)
+    const int per = views_per_block(n_views, blocks, degree);
+    const int chunks = (n_views + per - 1) / per;
+#define GS_PREV(D) hipLaunchKernelGGL(k_preprocess_views<D>, dim3(blocks, chunks), dim3(kBlock), 0, st, B, n_views, per, means, log_scales, q4, logits, sh, cams, set, splats, depth_keys, reinterpret_cast<uint2*>(tile_rects), partial)
     switch (degree) {
       case 0: GS_PREV(0); break;
       case 1: GS_PREV(1); break;

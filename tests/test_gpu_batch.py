@@ -263,3 +263,39 @@ def test_multi_view_backward_matches_per_view_backward(R):
     again = R.backward_views(p, cams, g2d, out=tuple(t.clone() for t in got), accumulate=True)
     for k in range(5):
         assert _rel_max(again[k], 2 * got[k]) <= 1e-6
+
+
+@pytest.mark.parametrize("counts,views,degree", [
+    ((1,), 1, 3), ((65, 0, 200), 3, 1), ((257,), 17, 3), ((64, 63, 300, 1), 9, 2),
+    ((1000,), 5, 0), ((700, 320), 33, 3), ((30_000, 7), 2, 3)])
+def test_batch_splits_of_views_and_assets(counts, views, degree):
+    """Each workgroup of the batch preprocess projects some of the views for
+    up to 256 Gaussians of one asset: wave and workgroup remainders, assets
+    without Gaussians, and view counts around the split, at every degree.
+    Images equal the view-by-view path's bitwise, gradients up to the order of
+    float atomics."""
+    from paper_2512_08478_amd.batch import BatchRenderer, plain_views
+    from paper_2512_08478_amd.render import GaussianParams
+    print_case(f"batch splits {counts} x {views} views, degree {degree}")
+    rng = np.random.default_rng(sum(counts) + views)
+    parts = []
+    for k, n in enumerate(counts):
+        sc, _ = S.tiny_scene(seed=k, n=max(n, 1))
+        q = GaussianParams.from_scene(sc)
+        sh = rng.normal(0.0, 0.3, (n, (degree + 1) ** 2, 3))
+        parts.append(GaussianParams(
+            *[t[:n].contiguous() for t in (q.means, q.log_scales, q.quats, q.opacity_logits)],
+            torch.tensor(sh, dtype=torch.float32, device="cuda"), degree,
+            [[1.0, 0.0, 0.0, 0.1 * k], [0.0, 1.0, 0.0, 0.0], [0.0, 0.0, 1.0, 0.0]]))
+    p = GaussianParams.concat(parts)
+    cams = [S.pinhole_camera(S.look_at((2.0 * np.sin(v), 0.3, -3.0 + 0.02 * v)), 64 + 8 * (v % 5),
+                             48 + 4 * (v % 3), 60.0) for v in range(views)]
+    tg = targets_for(cams)
+    imgs_ref, grads_ref = plain_views(p, cams, tg)
+    br = BatchRenderer(p, cams, tg)
+    imgs = br.run_eager()
+    for v in range(views):
+        assert torch.equal(imgs[v], imgs_ref[v]), v
+    for k, nm in enumerate(NAMES):
+        d = _rel_max(br.grads[k], grads_ref[k])
+        assert d <= 1e-5, (nm, d)
