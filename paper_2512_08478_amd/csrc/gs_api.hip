@@ -1203,25 +1203,10 @@ int32_t batch_enqueue(const gs_batch* b, char* ws, float* images, float* d_means
                                       st);
   if (e != hipSuccess) return hip_fail(e);
   gs::trace_mark(st, "preprocess_bwd");
-  const int K3 = (b->deg + 1) * (b->deg + 1) * 3;
-  const gs::SetK sk1 = make_setk(&b->cams[0], &b->set);
-  for (int a = 0; a < b->A && e == hipSuccess; ++a) {
-    const int64_t o = b->assets[a].offset, c = b->assets[a].count;
-    if (c == 0) continue;
-    for (int v0 = 0; v0 < b->V && e == hipSuccess; v0 += gs::kBwdViews) {
-      gs::ViewsK vk;
-      vk.nv = b->V - v0 < gs::kBwdViews ? b->V - v0 : gs::kBwdViews;
-      for (int k = 0; k < gs::kBwdViews; ++k) {
-        const int v = v0 + (k < vk.nv ? k : 0);
-        vk.cam[k] = b->camk[(size_t)v * b->A + a];
-        vk.g2d[k] = k < vk.nv ? g2d + gs::kGrad2dStride * ((int64_t)v * b->n + o) : nullptr;
-      }
-      e = gs::launch_preprocess_backward_views(
-          (int)c, b->means + 3 * o, b->log_scales + 3 * o, b->quats + 4 * o, b->logits + o,
-          b->sh + K3 * o, b->deg, vk, sk1, d_means + 3 * o, d_log_scales + 3 * o, d_quats + 4 * o,
-          d_opacity_logits + o, d_sh + K3 * o, v0 > 0 ? 1 : 0, st);
-    }
-  }
+  e = gs::launch_preprocess_backward_batch(
+      b->pre, b->V, b->means, b->log_scales, b->quats, b->logits, b->sh, b->deg,
+      reinterpret_cast<const gs::CamK*>(ws + L.camk), make_setk(&b->cams[0], &b->set), g2d, d_means,
+      d_log_scales, d_quats, d_opacity_logits, d_sh, st);
   if (e != hipSuccess) return hip_fail(e);
   gs::trace_mark(st, "");
   return GS_OK;

@@ -273,6 +273,12 @@ hipError_t launch_preprocess_backward(int n, const float* means, const float* lo
                                       float* d_means, float* d_log_scales, float* d_quats,
                                       float* d_logits, float* d_sh, int accumulate,
                                       hipStream_t st);
+hipError_t launch_preprocess_backward_batch(const BatchPreK& B, int n_views, const float* means,
+                                            const float* log_scales, const float* quats,
+                                            const float* logits, const float* sh, int degree,
+                                            const CamK* cams, const SetK& set, const float* grad2d,
+                                            float* d_means, float* d_log_scales, float* d_quats,
+                                            float* d_logits, float* d_sh, hipStream_t st);
 hipError_t launch_preprocess_backward_views(int n, const float* means, const float* log_scales,
                                             const float* quats, const float* logits,
                                             const float* sh, int degree, const ViewsK& views,
