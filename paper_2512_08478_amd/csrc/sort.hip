@@ -900,6 +900,20 @@ __global__ __launch_bounds__(PART) void k_kg_hist(uint32_t n, const uint32_t* __
   }
 }
 
+// The slice of the keygen's workgroup b (workgroups go to the 8 XCDs in turn):
+// runs of kKgXcdRun neighbouring slices share an XCD, so that the few
+// instances that each writes for a digit meet in one L2 instead of leaving it
+// in parts.  Whole eighths, as in xcd_part, would give one XCD all the nearest
+// slices, which hold the most instances (6M: 105 us in runs of 4, 107 of 16,
+// 115 of 64, 108 without; 144M Gaussians of 32 views 1,740, 1,730, 1,730 and
+// 2,590 us).
+constexpr uint32_t kKgXcdRun = 4;
+__device__ __forceinline__ uint32_t kg_slice(uint32_t b, uint32_t slices) {
+  constexpr uint32_t span = 8 * kKgXcdRun;
+  if (b >= slices / span * span) return b;  // the last, incomplete span
+  return b / span * span + b % 8 * kKgXcdRun + b / 8 % kKgXcdRun;
+}
+
 // Key generation fused with the first radix pass over the tile keys.  Each
 // slice's instances (depth order, then row-major within a rect) are
 // expanded in windows of WIN as in k_kg_write, ranked within the window by
@@ -911,7 +925,7 @@ __global__ __launch_bounds__(PART) void k_kg_hist(uint32_t n, const uint32_t* __
 // `cap` are skipped (capacity overflow); every position below it still
 // receives exactly one pair.
 //
-// Workgroup b < slices_grid expands slice b's first kKgChunk instances (all,
+// Workgroup b < slices_grid expands one slice's first kKgChunk instances (all,
 // but for heavy slices), the workgroups after them one further chunk of the
 // list each; where the list is full (only with more instances than the
 // capacity) the chunk before the missing ones runs to its slice's end.  A
@@ -951,6 +965,7 @@ __global__ __launch_bounds__(NT) void k_kg_scatter(const uint32_t* __restrict__ 
   uint32_t slice = blockIdx.x, chunk = 0;
   if (slice < slices_grid) {
     if (slice >= nsl) return;
+    slice = kg_slice(slice, nsl);
   } else {
     const uint32_t e = slice - slices_grid;
     if (e >= *heavy.count) return;
