@@ -611,6 +611,14 @@ int32_t gs_preprocess_backward_views(
     float* d_opacity_logits, float* d_sh, int32_t accumulate, void* stream);
 
 /*
+ * gs_l1_grad -- the gradient of L = mean over (H, W, 3) of |RGB - target| of
+ * one image: image and grad hold 4 floats per pixel (16-byte aligned), target
+ * 3; the alpha gradient is 0.
+ */
+int32_t gs_l1_grad(int64_t n_pixels, const float* image, const float* target, float* grad,
+                   void* stream);
+
+/*
  * Batches of views (Algorithm 1 renders every model with one global sort;
  * Section 4.5 argues for a single global order).  A batch renders
  * n_views cameras of one scene (an asset table over n Gaussians, as in

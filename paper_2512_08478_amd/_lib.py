@@ -33,7 +33,7 @@ EXPORTED = (
     "gs_workspace_size", "gs_sort_key_bits", "gs_preprocess", "gs_sort", "gs_sort_checked", "gs_sort_pairs",
     "gs_rasterize", "gs_rasterize_backward", "gs_trace_enable", "gs_trace_read",
     "gs_preprocess_assets", "gs_rasterize_backward_assets", "gs_rasterize_backward_2d",
-    "gs_preprocess_backward_views", "gs_sort_pairs32", "gs_packed_sh_stride", "gs_prepack",
+    "gs_preprocess_backward_views", "gs_l1_grad", "gs_sort_pairs32", "gs_packed_sh_stride", "gs_prepack",
     "gs_preprocess_packed", "gs_rasterize_mesh", "gs_rasterize_backward_2d_mesh", "gs_lbs_deform",
     "gs_preprocess_noalloc", "gs_preprocess_noalloc_max_n", "gs_sort_plan",
     "gs_raster_grid", "gs_raster_unit",
@@ -203,6 +203,8 @@ def load():
     lib.gs_preprocess_backward_views.argtypes = [I32, CAM, ctypes.POINTER(ctypes.c_void_p), I32, AS,
                                                  I64, P, P, P, P, P, I32, SET, P, P, P, P, P, I32,
                                                  P]
+    lib.gs_l1_grad.restype = I32
+    lib.gs_l1_grad.argtypes = [I64, P, P, P, P]
     lib.gs_packed_sh_stride.restype = I32
     lib.gs_packed_sh_stride.argtypes = [I32]
     lib.gs_prepack.restype = I32

@@ -34,9 +34,34 @@ SORT_MODES = (0, 1)
 RASTER_ORDERS = (1, 0, 3, 5, 2, 4)
 
 
+def _l1_in_kernel(image, target, H, W):
+    """Whether gs_l1_grad computes l1_grad(image, target): plain float32
+    tensors of the frame's layout on the current device, with nothing that
+    records or transforms the operations (autograd, torch.func, dispatch
+    modes, tracing)."""
+    for t in (image, target):
+        if type(t) is not torch.Tensor or t.dtype != torch.float32 or t.requires_grad:
+            return False
+    return (0 < H * W < 2**31 and target.shape == (H, W, 3) and image.shape == (H, W, 4) and
+            image.is_cuda and target.device == image.device and
+            image.device.index == torch.cuda.current_device() and
+            torch._C._functorch.peek_interpreter_stack() is None and
+            torch.autograd.forward_ad._current_level < 0 and
+            torch._C._len_torch_dispatch_stack() == 0 and
+            torch._C._len_torch_function_stack() == 0 and
+            not torch.jit.is_tracing() and not torch.compiler.is_compiling() and
+            image.is_contiguous() and target.is_contiguous() and
+            not image.is_neg() and not target.is_neg() and image.data_ptr() % 16 == 0)
+
+
 def l1_grad(image, target):
     """dL/dRGBA of L = mean |RGB - target| over (H, W, 3); alpha gets none."""
     H, W = target.shape[:2]
+    if _l1_in_kernel(image, target, H, W):
+        g = torch.empty((H, W, 4), dtype=torch.float32, device=image.device)
+        L.check(L.load().gs_l1_grad(H * W, image.data_ptr(), target.data_ptr(), g.data_ptr(),
+                                    torch.cuda.current_stream().cuda_stream), "gs_l1_grad")
+        return g
     g = torch.zeros((H, W, 4), dtype=torch.float32, device=image.device)
     g[..., :3] = torch.sign(image[..., :3] - target) / (3.0 * H * W)
     return g

@@ -1037,6 +1037,19 @@ int32_t gs_preprocess_backward_views(
   return GS_OK;
 }
 
+int32_t gs_l1_grad(int64_t n_pixels, const float* image, const float* target, float* grad,
+                   void* stream) {
+  int32_t r;
+  if (n_pixels < 0 || n_pixels > INT32_MAX) return GS_ERR_INVALID_ARGUMENT;
+  if (n_pixels == 0) return GS_OK;
+  if (!target) return GS_ERR_INVALID_ARGUMENT;
+  if ((r = check_dev(image)) || (r = check_dev(grad))) return r;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const hipError_t e = gs::launch_l1_grad(nullptr, 1, n_pixels, image, target, grad, st);
+  if (e != hipSuccess) return hip_fail(e);
+  gs::trace_mark(st, "");
+  return GS_OK;
+}
 
 // ---------------------------------------------------------------- batches of views
 

@@ -287,8 +287,9 @@ hipError_t launch_preprocess_backward_views(int n, const float* means, const flo
                                             int accumulate, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t count, hipStream_t st);
 // L1 loss gradient of every view of a batch (views: device table; image and
-// grad 4 floats per pixel, target 3, views concatenated).
-hipError_t launch_l1_grad(const ViewK* views, int n_views, int max_pixels, const float* image,
+// grad 4 floats per pixel, target 3, views concatenated); views NULL: one view
+// of max_pixels pixels.
+hipError_t launch_l1_grad(const ViewK* views, int n_views, int64_t max_pixels, const float* image,
                           const float* target, float* grad, hipStream_t st);
 
 // Opt-in kernel tracer: when enabled, trace_mark records a HIP event on the

@@ -170,3 +170,42 @@ def test_backward_group_remainders(R, orc, n):
         e = rel_l2(g[nm], g_ref[nm])
         print(f"{nm}: rel L2 {e:.2e}")
         assert e <= 1e-4, (nm, e)
+
+
+@pytest.mark.parametrize("h,w", [(1, 1), (1, 255), (16, 16), (1, 257), (250, 190), (800, 801)])
+def test_l1_grad_kernel_equals_elementwise_passes(h, w):
+    """l1_grad by the kernel is bitwise the elementwise form that it replaces,
+    with equal values, infinities and NaN among the pixels; what the kernel
+    does not take (float64, strided, misaligned or grad-requiring inputs) still
+    goes through that form."""
+    from paper_2512_08478_amd.batch import _l1_in_kernel, l1_grad
+    print_case(f"l1 gradient {h}x{w}")
+    g = torch.Generator(device="cuda").manual_seed(h * 1000 + w)
+    image = torch.rand(h, w, 4, generator=g, device="cuda")
+    target = torch.rand(h, w, 3, generator=g, device="cuda")
+    flat = target.view(-1)
+    flat[::7] = image[..., :3].reshape(-1)[::7]
+    flat[3::11] = float("inf")
+    flat[5::13] = float("nan")
+
+    def passes(image, target):
+        out = torch.zeros((h, w, 4), dtype=torch.float32, device=image.device)
+        out[..., :3] = torch.sign(image[..., :3] - target) / (3.0 * h * w)
+        return out
+
+    want = passes(image, target)
+    assert _l1_in_kernel(image, target, h, w)
+    got = l1_grad(image, target)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    wide = torch.rand(h * w * 4 + 1, generator=g, device="cuda")
+    others = [(image.double(), target.double()),
+              (wide[1:].view(h, w, 4), target),
+              (image.expand(2, h, w, 4).permute(1, 2, 3, 0)[..., 0].clone().requires_grad_(True), target),
+              (torch.rand(h, w, 5, generator=g, device="cuda")[..., :4], target)]
+    for im, tg in others:
+        if (h, w) == (1, 1) and im.stride() == image.stride() and im.dtype == image.dtype \
+                and not im.requires_grad and im.data_ptr() % 16 == 0:
+            continue
+        a, b = l1_grad(im, tg), passes(im, tg)
+        assert a.requires_grad == b.requires_grad and a.dtype == b.dtype
+        assert torch.equal(a.detach().view(torch.int32), b.detach().view(torch.int32))
