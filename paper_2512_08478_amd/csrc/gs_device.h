@@ -1,5 +1,5 @@
-// Device helpers for wave64 (gfx950): lane queries, ballots, wave scans
-// on the DPP paths and agent-scope atomic loads/stores for cross-workgroup
+// Device helpers for wave64 (gfx950): lane queries, ballots, wave scans,
+// DPP group sums and agent-scope atomic loads/stores for cross-workgroup
 // look-back.
 #pragma once
 
@@ -28,6 +28,26 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   const int l = lane_id();
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += shfl_u32(v, l ^ d);
+  return v;
+}
+
+// x from another lane of the same 16-lane row by the DPP control CTRL
+// (lanes whose source is outside the row read 0).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_f32(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xF, true));
+}
+
+// Sum of v over each group of 8 lanes, left in the group's last lane (7,
+// 15, ..., 63): DPP row shifts by 1, 2 and 4 accumulate the 8 lanes ending
+// at each lane, and lanes shifted in from outside a 16-lane row read 0.  (v is
+// rounded before it is added: fused with the first addition it would differ
+// between the two lanes of a pair, and take an instruction more.)
+__device__ __forceinline__ float oct_sum_dpp(float v) {
+#pragma clang fp contract(off)
+  v += dpp_f32<0x111, 0xF>(v);  // row_shr:1
+  v += dpp_f32<0x112, 0xF>(v);  // row_shr:2
+  v += dpp_f32<0x114, 0xF>(v);  // row_shr:4
   return v;
 }
 

@@ -488,33 +488,30 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
 // recovering T_i = T_{i+1} / (1 - alpha_i) from T_final.  With
 //   S_i = colour composited behind i (normalised by T_{i+1}),
 //   B_i = T_final / T_{i+1},
-// dL/dalpha_i = T_i (dC . (c_i - S_i - B_i bg) + dA B_i)
-//             = T_i (dC . c_i - R_i),  R_i = dC . S_i + B_i (dC . bg - dA),
-// and R needs no more than one fma per splat:
-//   R_{i-1} = R_i + alpha_i (dC . c_i - R_i).
+// dC/dalpha_i = T_i (c_i - S_i - B_i bg) and dA/dalpha_i = T_i B_i.
 //
-// A splat's 9 gradient sums over the quadrant's 64 pixels are products with
-// matrices that do not depend on the splat: with w = alpha T the blend
-// weight and q = dL/de (e: the log2 weight),
-//   dL/drgb = sum_p w(p) dC(p),
-// and, as e is a quadratic in the pixel's offset (x, y) from a centre, the
-// other six follow from the moments sum_p q(p) x^a y^b, a + b <= 2.  So each
-// splat leaves its q and w of the 64 pixels in LDS, and once kGroup splats
-// are together 16 fp32 MFMAs (16x16x4) multiply the 16 features of the
-// pixels with the pixels' q and w.  The features are dC and the monomials
-// about each of the four quarters' centres, 16 in all, and a splat's sums
-// are formed from those about the centre nearest its mean, so that they
-// cancel little even for the smallest splats (sigma 0.55 px; moments about
-// the quadrant's centre made the gradients of such scenes 2-3 times less
-// accurate than per-pixel sums).
+// Per pixel, with dQ = dL/dQ' of the weight 2^(log2(o) - Q'),
+// Q' = qa' u^2 + qc' dy^2, u = dx - qb dy, the 9 partial derivatives are
+//   mean x: -2 dQ qa' u      mean y: 2 dQ (qa' u qb - qc' dy)
+//   qa: c dQ u^2             qb: -2 dQ qa' u dy
+//   qc: c dQ dy^2            opacity: -dQ / (ln2 o)     rgb: alpha T dC
+// (c = log2(e) / 2).  dy is the same for the 8 pixels of a row, so a row's 9
+// sums follow from its sums of dQ, dQ qa' u, dQ u^2 and the 3 colour terms:
+// each visit adds these 6 up with DPP and leaves them in LDS, and once
+// kGroup splats are together a lane per splat and row forms the 9 values, DPP
+// adds the 8 rows up and one atomic instruction sends the group's 63 sums.
 //
-// Bound: vector and matrix issue (they share it: a variant without the MFMAs
-// saved their whole 32 cycles each).  Summing 9 values with DPP row shifts,
-// an LDS exchange and one atomic per splat took ~130 vector instructions per
-// (splat, quadrant) visit; here a visit takes ~27 and its share of a group
-// ~8 and 2.4 MFMAs, and one atomic instruction sends a group's 63 values.
-// Measured: 500k Gaussians at 800x800, 32x16 tiles, 247 -> 195 us; 32 views
-// of 4.5M, 16x8 tiles, 11.9 -> 9.7 ms; 20k at 250x190, 138 -> 91 us.
+// (The sums must be formed from each pixel's own u and dy.  Moments of dQ about
+// fixed centres, as matrix products give them, cancel: on splats of 0.55 px and
+// on thin ones of 3 to 30 px the rms errors of the mean and qa, qb, qc sums
+// were 1.4 to 5.5 times those of this form, which are a plain float32
+// evaluation's.)
+//
+// Bound: vector issue.  With each splat's 9 values formed, exchanged and sent
+// as soon as it was visited, a visit took ~130 vector instructions; here ~55,
+// and its share of a group ~11.  Measured: 500k Gaussians at 800x800, 32x16
+// tiles, 247 -> 208 us; 32 views of 4.5M, 16x8 tiles, 11.9 -> 9.6 ms; 20k at
+// 250x190, 138 -> 98 us.
 //
 // Each 8x8 quadrant of a TW x TH tile is its own one-wave workgroup that
 // walks the tile's whole list (skipping splats that miss the quadrant), so
@@ -522,24 +519,9 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
 // here is heavy, and small workgroups balance it across the CUs far better
 // than one workgroup per tile.  A quadrant stages exactly the row terms the
 // forward kernel used for its pixels, so every skip decision matches.
-constexpr int kGroup = 7;         // splats per matrix product: 7 x 9 values fill one atomic
-constexpr int kPixStride = 68;    // floats per w / q row (64 pixels, padded: the rows of one
-                                  // 16-byte column lie in different banks)
-constexpr int kVals = 9;          // gradient values per splat
-constexpr int kSumStride = 12;    // floats per splat of its sums in LDS
-using f32x4 = __attribute__((ext_vector_type(4))) float;
-
-// Lanes 0..15 get x of lanes 16..31.
-__device__ __forceinline__ float next_row(float x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[1]);
-}
-
-// Lanes 0..31 get x of lanes 32..63.
-__device__ __forceinline__ float upper_half(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[1]);
-}
+constexpr int kGroup = 7;       // splats whose sums are formed together: 7 x 9 values fill one atomic
+constexpr int kVals = 9;        // gradient values per splat
+constexpr int kSumStride = 12;  // floats per splat of its sums in LDS
 
 // The staged splats of the backward walk, in walk order (back to front).
 constexpr int kStaged = 32;
@@ -548,13 +530,10 @@ struct StageB {
   float2 rows[kStaged][8];  // as in StageT
   float4 aux[kStaged];      // qb, qc', dy at the quadrant's first row, 1 / opacity
   uint32_t gid[kStaged];    // Gaussian index
-  uint32_t ctr[kStaged];    // its moments' centre: bit 0, x = +2 (else -2); bit 1, y
 };
 
 template <int TW, int TH>
-// at least 2 waves per SIMD: the compiler then keeps the MFMA accumulators in
-// plain VGPRs (with a 1-wave budget it uses accumulation VGPRs and moves)
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_raster_bwd(const gs_splat* __restrict__ splats,
+__global__ __launch_bounds__(64) void k_raster_bwd(const gs_splat* __restrict__ splats,
                                                    const uint32_t* __restrict__ values,
                                                    const uint32_t* __restrict__ ranges,
                                                    SetK set, int W, int H,
@@ -565,9 +544,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
                                                    float* __restrict__ grad2d) {
   constexpr int QX = TW / 8, NQ = (TW / 8) * (TH / 8);
   __shared__ StageB S;
-  // rows 0..kGroup-1: q of the group's splats, rows 8..8+kGroup-1: w; then
-  // (rows read) the group's kGroup x 9 sums
-  __shared__ __attribute__((aligned(16))) float s_p[16 * kPixStride];
+  // the group's sums over each pixel row: dQ, dQ qa' u, dQ u^2, r | g, b
+  __shared__ float4 s_row[kGroup][8][2];
+  __shared__ float4 s_sum[kGroup * kSumStride / 4];
   int tile, q, band;
   if (!pick_unit<NQ, false>(blockIdx.x, set, ranges, tile, q, band)) return;
   int trow = tile / set.tiles_x;
@@ -611,112 +590,46 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
   for (int d = 32; d >= 1; d >>= 1) nlast = max(nlast, shfl_u32(nlast, lane ^ d));
   nlast = __builtin_amdgcn_readfirstlane(nlast);
   if (nlast == 0) return;
-  float R = dC0 * b0 + dC1 * b1 + dC2 * b2 - dA;
-
-  // The matrix of the pixels, in the layout of the MFMA's A operand: step t
-  // (0..15), lane (16 k + j) holds feature j of pixel 16 k + t.  With x, y the
-  // pixel's offset from the quadrant's centre and x-, x+ = x + 2, x - 2:
-  //   0: 1      1..3: dC     4..7: x-, x+, y-, y+
-  //   8..11: x-^2, x+^2, y-^2, y+^2    12..15: x- y-, x- y+, x+ y-, x+ y+
-  const int col = lane & 15, kq = lane >> 4;
-  float feat[16];
-  s_p[lane] = dC0;
-  s_p[kPixStride + lane] = dC1;
-  s_p[2 * kPixStride + lane] = dC2;
-  __syncthreads();
-  {
-    const int grp = col >> 2, var = col & 3;
-    const bool fx = grp == 3 || (grp > 0 && var < 2), fy = grp == 3 || (grp > 0 && var >= 2);
-    const float cx = (grp == 3 ? var >= 2 : var == 1) ? 2.f : -2.f;
-    const float cy = (var & 1) ? 2.f : -2.f;
-    // the feature is px(x) py(y), each 1, the offset or its square
-    auto power = [&](float d, bool on) { return on ? (grp == 2 ? d * d : d) : 1.f; };
-    const float yk = 2.f * (float)kq - 3.5f - cy;  // rows 2 k and 2 k + 1
-    const float py[2] = {power(yk, fy), power(yk + 1.f, fy)};
-    float pxs[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) pxs[i] = power((float)i - 3.5f - cx, fx);
-    const bool colour = grp == 0 && var > 0;
-    const float4* src =
-        reinterpret_cast<const float4*>(s_p + (colour ? var - 1 : 0) * kPixStride + 16 * kq);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float4 g = src[t];
-      const float gc[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        feat[4 * t + i] = colour ? gc[i] : pxs[(4 * t + i) & 7] * py[t >> 1];
-    }
-  }
-  __syncthreads();
+  const float bgdot = dC0 * b0 + dC1 * b1 + dC2 * b2;
+  float S0 = 0.f, S1 = 0.f, S2 = 0.f, B = 1.f;
 
   // the value this lane sends for a group: value lane % 9 of its splat lane / 9
   const int vslot = lane / kVals, vj = lane - vslot * kVals;
-  // Sums of the group's first `ns` splats (staged splats kpack, one byte
-  // each), added to their 2-D gradient records.  (The wave's LDS accesses
-  // execute in order; the barriers only keep the compiler from moving them.)
+  // The 9 sums of the group's first `ns` splats (staged splats kpack, one byte
+  // each) from their row sums, added to their 2-D gradient records: lane
+  // 8 s + r takes row r of splat s.  (The wave's LDS accesses execute in order;
+  // the barriers only keep the compiler from moving them.)
   auto flush = [&](int ns, uint64_t kpack) {
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
-    const float4* ap = reinterpret_cast<const float4*>(s_p + col * kPixStride + 16 * kq);
-    const float4 a[4] = {ap[0], ap[1], ap[2], ap[3]};
-    // lanes 0..7 form the geometry sums of splat `lane`; lanes 8..15 hold the
-    // colour sums of splat `lane - 8`
-    const int k = (int)(kpack >> (8 * (lane & 7))) & (kStaged - 1);
-    const uint32_t ctr = S.ctr[k];
-    const bool sx = ctr & 1u, sy = ctr & 2u;
-    const float4 x = S.aux[k];  // qb, qc', dy at the quadrant's first row, 1 / opacity
-    const float qa = S.hdr[k].x;
-    const float ub = S.rows[k][sy ? 5 : 1].y;
+    const int slot = min(row, kGroup - 1);
+    const int k = (int)(kpack >> (8 * slot)) & (kStaged - 1);
     const uint32_t gid = S.gid[(int)(kpack >> (8 * vslot)) & (kStaged - 1)];
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+    const float4 x = S.aux[k];  // qb, qc', dy at the quadrant's first row, 1 / opacity
+    const float4 a = s_row[slot][lx][0], b = s_row[slot][lx][1];
+    const float sQ = a.x, sA = a.y, sU = a.z;
+    const float dy = x.z + lxf;
+    float v[kVals] = {-2.f * sA, 2.f * (sA * x.x - (x.y * dy) * sQ), kHalfLog2e * sU,
+                      -2.f * dy * sA, kHalfLog2e * (dy * dy) * sQ, -sQ * x.w * (1.f / kLn2),
+                      a.w, b.x, b.y};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t], a[t].x, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t + 1], a[t].y, acc1, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t + 2], a[t].z, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(feat[4 * t + 3], a[t].w, acc1, 0, 0, 0);
+    for (int j = 0; j < kVals; ++j) {
+      v[j] = oct_sum_dpp(v[j]);
+      asm volatile("" : "+v"(v[j]));
     }
-    // features 4 kq + r (lane row kq) of column `col`: q of splat col, or w
-    // of splat col - 8.  Each lane row picks its splat's centre's features,
-    // then row 0 gets them all.
-    const f32x4 acc = acc0 + acc1;
-    float gx = sx ? acc[1] : acc[0], gy = sy ? acc[3] : acc[2];  // rows 1, 2: x, y | x^2, y^2
-    float gxy = sx ? (sy ? acc[3] : acc[2]) : (sy ? acc[1] : acc[0]);  // row 3
-    const float m00 = acc[0], m10 = next_row(gx), m01 = next_row(gy);
-    const float m20 = upper_half(gx), m02 = upper_half(gy), m11 = upper_half(next_row(gxy));
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
-    if (lane < 8) {
-      // u = dx - qb dy and dy at the centre
-      const float U = fmaf(-0.5f, x.x, ub + (sx ? 5.5f : 1.5f)), D = x.z + (sy ? 5.5f : 1.5f);
-      const float su = fmaf(U, m00, fmaf(-x.x, m01, m10));   // sum q u
-      const float sux = fmaf(U, m10, fmaf(-x.x, m11, m20));  // sum q u x
-      const float suy = fmaf(U, m01, fmaf(-x.x, m02, m11));  // sum q u y
-      const float suu = fmaf(U, su, fmaf(-x.x, suy, sux));   // sum q u^2
-      const float sd = fmaf(D, m00, m01);                  // sum q dy
-      const float sdd = fmaf(D, sd, fmaf(D, m01, m02));  // sum q dy^2
-      const float sud = fmaf(D, su, suy);                  // sum q u dy
-      // q = dL/de = ln2 w' dL/dw' per pixel was stored without the ln2, and
-      // e = log2(o) - qa' u^2 - qc' dy^2, u = dx - qb dy, dx = px + 1/2 - mean x
-      const float au = (2.f * kLn2) * qa * su;
-      float4* v = reinterpret_cast<float4*>(s_p + lane * kSumStride);
-      v[0] = make_float4(au,                                       // mean x
-                         fmaf((2.f * kLn2) * x.y, sd, -x.x * au),  // mean y
-                         (-kLn2 * kHalfLog2e) * suu,               // qa
-                         (2.f * kLn2) * qa * sud);                 // qb
-      *reinterpret_cast<float2*>(v + 1) =
-          make_float2((-kLn2 * kHalfLog2e) * sdd,                  // qc
-                      m00 * x.w);                                  // opacity
-    } else if (lane < 16) {
-      float* v = s_p + (lane - 8) * kSumStride + 6;
-      *reinterpret_cast<float2*>(v) = make_float2(acc[1], acc[2]);
-      v[2] = acc[3];
+    if (lx == 7 && row < kGroup) {
+      float4* dst = s_sum + row * (kSumStride / 4);
+      dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+      dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+      dst[2].x = v[8];
     }
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
     if (lane < ns * kVals)
-      atomicAdd(grad2d + (size_t)gid * kGrad2dStride + vj, s_p[vslot * kSumStride + vj]);
+      atomicAdd(grad2d + (size_t)gid * kGrad2dStride + vj,
+                reinterpret_cast<const float*>(s_sum)[vslot * kSumStride + vj]);
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
   };
@@ -725,28 +638,39 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
   int skip = 0;    // of them, the first `skip` lie at or past this pixel's `last`
   int ns = 0;      // splats in the group
   uint64_t kpack = 0;
-  // One staged splat's visit.  Lanes never branch apart: a pair a lane must
+  // One staged splat's visit: the back-to-front state update and the row sums
+  // of the lanes' gradient terms.  Lanes never branch apart: a pair a lane must
   // not revisit (at or past its `last`, or weight below alpha_min) gets
-  // alpha = 0, which leaves T and R bitwise unchanged and yields zero
+  // alpha = 0, which leaves T, S and B bitwise unchanged and yields zero
   // gradients.
-  auto visit = [&](int k, float e, const float4& h) {
+  auto visit = [&](int k, float u, float e, const float4& h) {
     const bool take = k >= skip && e >= log2_tau;
     if (!ballot(take)) return;
     const float gw = take ? hw_exp2(e) : 0.f;
     const float alpha = __builtin_amdgcn_fmed3f(gw, 0.f, amax);  // as the forward
-    // T before this splat, T / (1 - alpha): the hardware reciprocal's product
-    // and one correction step (its errors would add up over the walk; exact
-    // where alpha = 0).  1 - alpha >= 1 - alpha_max, far from 0.
-    const float om = 1.f - alpha, rc = __builtin_amdgcn_rcpf(om), Tr = T * rc;
-    const float Ti = fmaf(fmaf(-om, Tr, T), rc, Tr);
-    const float d = fmaf(dC2, h.w, fmaf(dC1, h.z, dC0 * h.y)) - R;
-    // no gradient flows through alpha where the alpha_max clamp binds
-    const float dal = take && gw < amax ? Ti * d : 0.f;
-    R = fmaf(alpha, d, R);
+    const float om = 1.f - alpha;
+    // T before this splat; 1 - alpha >= 1 - alpha_max, far from 0
+    const float Ti = take ? T * __builtin_amdgcn_rcpf(om) : T;
+    const float cr = h.y, cg = h.z, cb = h.w;
+    const float w = alpha * Ti;
+    const float dalpha = Ti * (dC0 * (cr - S0) + dC1 * (cg - S1) + dC2 * (cb - S2) -
+                               B * bgdot + dA * B);
+    S0 = fmaf(alpha, cr - S0, S0);
+    S1 = fmaf(alpha, cg - S1, S1);
+    S2 = fmaf(alpha, cb - S2, S2);
+    B *= om;
     T = Ti;
-    float* dst = s_p + ns * kPixStride + lane;
-    dst[0] = gw * dal;
-    dst[8 * kPixStride] = alpha * Ti;
+    // no gradient flows through alpha where the alpha_max clamp binds
+    const float dal = take && gw < amax ? dalpha : 0.f;
+    const float tq = -kLn2 * gw * dal;
+    float sQ = oct_sum_dpp(tq), sA = oct_sum_dpp(tq * (h.x * u)), sU = oct_sum_dpp(tq * (u * u));
+    float sr = oct_sum_dpp(dC0 * w), sg = oct_sum_dpp(dC1 * w), sb = oct_sum_dpp(dC2 * w);
+    // (the last additions stay on the DPP path, outside the branch)
+    asm volatile("" : "+v"(sQ), "+v"(sA), "+v"(sU), "+v"(sr), "+v"(sg), "+v"(sb));
+    if (lx == 7) {
+      s_row[ns][row][0] = make_float4(sQ, sA, sU, sr);
+      *reinterpret_cast<float2*>(&s_row[ns][row][1]) = make_float2(sg, sb);
+    }
     kpack |= (uint64_t)k << (8 * ns);
     if (++ns == kGroup) {
       flush(kGroup, kpack);
@@ -784,7 +708,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
         const QuadTerms t(r_cur, tx0, ty0);
         S.hdr[k] = make_float4(t.qa, r_cur.b.z, r_cur.b.w, r_cur.c);
         S.aux[k] = make_float4(t.qb, t.qc, t.uy, 1.f / r_cur.b.y);
-        S.ctr[k] = (t.ux < -3.5f ? 1u : 0u) | (t.uy < -3.5f ? 2u : 0u);
         S.gid[k] = g_cur;
         t.rows(S.rows[k]);
       }
@@ -807,11 +730,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
     for (int k0 = 0; k0 < staged; k0 += 2) {
       const float2 q0 = S.rows[k0][row], q1 = S.rows[k0 + 1][row];
       const float4 h0 = S.hdr[k0], h1 = S.hdr[k0 + 1];
+      // (read here, not within the visits)
+      asm volatile("" ::"v"(h0.y), "v"(h0.z), "v"(h0.w), "v"(h1.y), "v"(h1.z), "v"(h1.w));
       const float u0 = q0.y + lxf, u1 = q1.y + lxf;
       const float e0 = fmaf(-h0.x, u0 * u0, q0.x);
       const float e1 = fmaf(-h1.x, u1 * u1, q1.x);
-      visit(k0, e0, h0);
-      if (k0 + 1 < staged) visit(k0 + 1, e1, h1);
+      visit(k0, u0, e0, h0);
+      if (k0 + 1 < staged) visit(k0 + 1, u1, e1, h1);
     }
     if (ns > 0) flush(ns, kpack);
     ns = 0;
