@@ -790,19 +790,46 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
   }
 }
 
+// The input gradients of one Gaussian.
+template <int DEG>
+struct ChainSums {
+  static constexpr int K3 = (DEG + 1) * (DEG + 1) * 3;
+  float p[3], ls[3], q[4], logit, sh[K3];
+  template <class F>
+  __device__ __forceinline__ void each(const ChainSums& o, F f) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { f(p[k], o.p[k]); f(ls[k], o.ls[k]); }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f(q[k], o.q[k]);
+    f(logit, o.logit);
+#pragma unroll
+    for (int k = 0; k < K3; ++k) f(sh[k], o.sh[k]);
+  }
+  __device__ __forceinline__ void clear() {
+    each(*this, [](float& a, float) { a = 0.f; });
+  }
+  __device__ __forceinline__ void add(const ChainSums& o) {
+    each(o, [](float& a, float b) { a += b; });
+  }
+};
+
 // The chain rule of a whole batch in one launch: every asset (workgroups of
 // one wave, four to a block of the asset table) and, in a loop, every view.
-// The gradients stay in registers over all views and are written once; the
-// SH rows stay in LDS (as in k_preprocess_views) and become the rows of their
-// gradients at the end, so that these leave in whole 16-byte vectors side by
-// side.  View v's records start at v * B.n rows; cams[v * n_assets + a].
+// The gradients stay in registers over all views and are written once; with
+// BLOCKS (more than kBwdViews views) those of kBwdViews views at a time are
+// summed by themselves before they join the total, which one running sum would
+// round at its full size for every view.  The SH rows stay in LDS (as in
+// k_preprocess_views) and become the rows of their gradients at the end, so
+// that these leave in whole 16-byte vectors side by side.  View v's records
+// start at v * B.n rows; cams[v * n_assets + a].
 // Bound: vector issue, then the records (48 bytes per view and Gaussian).
-// Measured against a launch per asset and 8 views, each adding its 236-byte
-// gradients to those before: 32 views of 4.5M in 9 assets, 5.2 -> 3.0 ms (with
-// 2 waves per SIMD and no spill 3.3 ms).
+// Measured: 32 views of 4.5M in 9 assets 3.7 ms, against 5.2 ms with a launch
+// per asset and 8 views, each adding its 236-byte gradients to those before (one
+// running sum over all views, 3 waves per SIMD: 3.05 ms; the sums of 8 views
+// added up in memory by one launch: 4.8 ms).
 constexpr int kChainThreads = 64;
-template <int DEG>
-__global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_preprocess_bwd_batch(
+template <int DEG, bool BLOCKS>
+__global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(BLOCKS && DEG == 3 ? 2 : 3, 8))) void k_preprocess_bwd_batch(
     BatchPreK B, int n_views, const float* __restrict__ means,
     const float* __restrict__ log_scales, const float4* __restrict__ quats,
     const float* __restrict__ logits, const float* __restrict__ sh,
@@ -834,14 +861,19 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(3
     }
     __syncthreads();
   }
-  float gp[3] = {0.f, 0.f, 0.f}, gls[3] = {0.f, 0.f, 0.f}, gq[4] = {0.f, 0.f, 0.f, 0.f};
-  float glogit = 0.f;
-  float gsh[K * 3];
-#pragma unroll
-  for (int k = 0; k < K * 3; ++k) gsh[k] = 0.f;
+  ChainSums<DEG> g;
+  g.clear();
   ChainIn in(live ? i : i0, means, log_scales, quats, logits);
   const float* rec = grad2d + (o + (live ? i : i0)) * kGrad2dStride;
+  ChainSums<DEG> total;  // of the blocks of views before
+  if constexpr (BLOCKS) total.clear();
   for (int v = 0; v < n_views; ++v, rec += B.n * kGrad2dStride) {
+    if constexpr (BLOCKS) {
+      if (v > 0 && v % kBwdViews == 0) {
+        total.add(g);
+        g.clear();
+      }
+    }
     const float4* r = reinterpret_cast<const float4*>(rec);
     const float4 x = r[0], y = r[1];
     const float z = r[2].x;
@@ -856,14 +888,18 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(3
     asm volatile("" : "+v"(in.qw), "+v"(in.qx), "+v"(in.qy), "+v"(in.qz), "+v"(in.s[0]),
                  "+v"(in.s[1]), "+v"(in.s[2]), "+v"(in.o));
     if constexpr (STAGED)
-      chain_one<DEG>(in, LdsRow<DEG>{s_sh + lane * STRIDE}, cam, set, G, gp, gls, gq, glogit, gsh);
+      chain_one<DEG>(in, LdsRow<DEG>{s_sh + lane * STRIDE}, cam, set, G, g.p, g.ls, g.q, g.logit, g.sh);
     else
-      chain_one<DEG>(in, GlobalRow<DEG>{sh, i}, cam, set, G, gp, gls, gq, glogit, gsh);
+      chain_one<DEG>(in, GlobalRow<DEG>{sh, i}, cam, set, G, g.p, g.ls, g.q, g.logit, g.sh);
+  }
+  if constexpr (BLOCKS) {
+    total.add(g);
+    g = total;
   }
   if constexpr (STAGED) {
 #pragma unroll
     for (int j = 0; j < F4; ++j)
-      s_sh[lane * STRIDE + j] = make_float4(gsh[4 * j], gsh[4 * j + 1], gsh[4 * j + 2], gsh[4 * j + 3]);
+      s_sh[lane * STRIDE + j] = make_float4(g.sh[4 * j], g.sh[4 * j + 1], g.sh[4 * j + 2], g.sh[4 * j + 3]);
     __syncthreads();
     float4* dst = reinterpret_cast<float4*>(d_sh) + (size_t)i0 * F4;
 #pragma unroll
@@ -875,14 +911,14 @@ __global__ __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(3
   if (!live) return;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    d_means[3 * i + k] = gp[k];
-    d_log_scales[3 * i + k] = gls[k];
+    d_means[3 * i + k] = g.p[k];
+    d_log_scales[3 * i + k] = g.ls[k];
   }
-  d_quats[i] = make_float4(gq[0], gq[1], gq[2], gq[3]);
-  d_logits[i] = glogit;
+  d_quats[i] = make_float4(g.q[0], g.q[1], g.q[2], g.q[3]);
+  d_logits[i] = g.logit;
   if constexpr (!STAGED) {
 #pragma unroll
-    for (int k = 0; k < K * 3; ++k) d_sh[(size_t)i * K * 3 + k] = gsh[k];
+    for (int k = 0; k < K * 3; ++k) d_sh[(size_t)i * K * 3 + k] = g.sh[k];
   }
 }
 
@@ -1005,7 +1041,7 @@ hipError_t launch_preprocess_backward_batch(const BatchPreK& B, int n_views, con
   if (blocks == 0 || n_views < 1) return hipSuccess;
   const float4* q4 = reinterpret_cast<const float4*>(quats);
   float4* dq4 = reinterpret_cast<float4*>(d_quats);
-#define GS_PBWDB(D) hipLaunchKernelGGL(k_preprocess_bwd_batch<D>, dim3(blocks), dim3(kChainThreads), 0, st, B, n_views, means, log_scales, q4, logits, sh, cams, set, grad2d, d_means, d_log_scales, dq4, d_logits, d_sh)
+#define GS_PBWDB(D) hipLaunchKernelGGL((n_views > kBwdViews ? k_preprocess_bwd_batch<D, true> : k_preprocess_bwd_batch<D, false>), dim3(blocks), dim3(kChainThreads), 0, st, B, n_views, means, log_scales, q4, logits, sh, cams, set, grad2d, d_means, d_log_scales, dq4, d_logits, d_sh)
   switch (degree) {
     case 0: GS_PBWDB(0); break;
     case 1: GS_PBWDB(1); break;

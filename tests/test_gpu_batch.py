@@ -299,3 +299,31 @@ def test_batch_splits_of_views_and_assets(counts, views, degree):
     for k, nm in enumerate(NAMES):
         d = _rel_max(br.grads[k], grads_ref[k])
         assert d <= 1e-5, (nm, d)
+
+
+@pytest.mark.parametrize("views,degree", [(8, 3), (9, 3), (33, 3), (33, 1), (20, 2), (17, 0)])
+def test_batch_gradients_sum_views_in_blocks(R, views, degree):
+    """The batch's chain rule sums the gradients of 8 views at a time before
+    they join the total, as the view-by-view entry point does: with frames of
+    one 8x8 quadrant, where no two atomics meet in a record, both give the same
+    bits."""
+    from paper_2512_08478_amd.batch import BatchRenderer, l1_grad
+    from paper_2512_08478_amd.render import GaussianParams
+    print_case(f"batch chain rule, {views} views, degree {degree}")
+    n = 130
+    sc, _ = S.fd_scene(seed=views, n=n, degree=degree)
+    sc.means[:] = 0.3 * sc.means
+    p = GaussianParams.concat([GaussianParams.from_scene(sc)])
+    cams = [S.pinhole_camera(S.look_at((2.0 * np.sin(v), 0.3, -3.0 + 0.02 * v)), 8, 8, 40.0)
+            for v in range(views)]
+    tg = targets_for(cams)
+    br = BatchRenderer(p, cams, tg)
+    br.run_eager()
+    g2d = []
+    for cam, t in zip(cams, tg):
+        fr = R.forward(p, cam, reuse=False)
+        g2d.append(R.backward_2d(p, cam, fr, l1_grad(fr.image, t)))
+    want = R.backward_views(p, cams, g2d)
+    for nm, a, b in zip(NAMES, br.grads, want):
+        assert float(b.abs().max()) > 0
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (nm, float((a - b).abs().max()))
