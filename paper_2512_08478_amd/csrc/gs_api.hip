@@ -642,7 +642,7 @@ int32_t sort_impl(int64_t n, const gs_splat* splats, const uint32_t* depth_keys,
     uint32_t* fk = pt > 1 ? U(L.tk[0]) : U(L.tkf);
     uint32_t* fv = pt > 1 ? U(L.tv[0]) : values;
     e = gs::launch_keygen_fused(n, capacity, bits, U(L.dv[0]), counts + 1, rects, drect, tiles_x,
-                                count, U(L.table), U(L.totals), U(L.tickets), U(L.kg_counts),
+                                count, U(L.kg_table), U(L.totals), U(L.tickets), U(L.kg_base),
                                 reinterpret_cast<uint2*>(ws + L.kg_list), L.kg_list_max, fk, fv,
                                 st);
     if (e != hipSuccess) return hip_fail(e);
@@ -1103,7 +1103,9 @@ BatchLayout batch_layout(const gs_batch* b, int64_t capacity) {
   L.recs = take((size_t)vn * sizeof(gs_splat));
   L.dkeys = take((size_t)vn * 4);
   L.rects = take((size_t)vn * 8);
-  L.partial = take((size_t)gs::preprocess_views_slots(b->V, b->pre.block0[b->A], b->deg) * 16);
+  // a slot per view and block: at least as many as the split of the views into
+  // workgroups takes, and never fewer for a larger batch
+  L.partial = take((size_t)b->V * b->pre.block0[b->A] * 16);
   L.counts = take(16);
   L.T = take((size_t)b->pixels * 4);
   L.last = take((size_t)b->pixels * 4);

@@ -81,10 +81,11 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // gs_sort workspace: depth ping-pong (u32 keys/values, n each), tile
 // ping-pong and final tile keys (u32, capacity each), onesweep histograms,
 // tickets and look-back words (two buffers), the reduce-then-scan count
-// table and digit totals, keygen slice counts, the kept instance count.
+// table and digit totals, keygen slice counts, the kept instance count.  The
+// fused keygen's kg_table, kg_base and kg_list lie in buffers that are idle then.
 struct SortLayout {
   size_t dk[2], dv[2], drect, tk[2], tv[2], tkf, hist, tickets, lookback, table, totals, kg_counts,
-      kg_list, count, tcls, tseg;
+      kg_table, kg_base, kg_list, count, tcls, tseg;
   size_t bytes;
   int parts;     // 4096-key partitions of the largest sort
   int rs_parts;  // 1024-key partitions of the largest sort (reduce-then-scan table rows)
@@ -229,14 +230,14 @@ hipError_t launch_radix_sort_widths(const RadixArgs<uint32_t>& a, const int* wid
                                     bool last_keys, const char* label, hipStream_t st);
 // Key generation fused with the first tile-digit pass (reduce-then-scan
 // mode): the first-digit histogram of each slice (with the rect gather),
-// the list of the heavy slices' chunks (kg_counts, kg_list, heavy_count: a
+// the list of the heavy slices' chunks (kg_base, kg_list, heavy_count: a
 // word that the set-up has cleared), its column scan into table/totals, and
 // the instances written in the order of that pass to tkeys/tvals.
 hipError_t launch_keygen_fused(int64_t n, int64_t capacity, int bits, const uint32_t* sorted_idx,
                                const uint32_t* vis_count, const uint2* rects,
                                uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
                                uint32_t* table, uint32_t* totals, uint32_t* heavy_count,
-                               uint32_t* kg_counts, uint2* kg_list, uint32_t kg_list_max,
+                               uint32_t* kg_base, uint2* kg_list, uint32_t kg_list_max,
                                uint32_t* tkeys, uint32_t* tvals, hipStream_t st);
 // Host mirror of the compositing kernels' work split (the same function
 // the kernels run): their grid, and the (tile, quadrant, band) workgroup b

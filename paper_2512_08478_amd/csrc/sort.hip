@@ -1407,21 +1407,28 @@ SortLayout sort_layout(int64_t n, int64_t capacity, int tiles) {
   L.hist = take((size_t)kMaxPassTotal * 256 * 4);
   L.tickets = take((size_t)kMaxPassTotal * 4);
   L.lookback = take((size_t)2 * L.parts * 256 * 4);
-  // rows of the radix partitions (up to 512 digits) or of the keygen slices
-  // (up to 256)
-  const int part = kg_part(nn, cap);
-  const size_t kg_rows = (size_t)((nn + part - 1) / part);
-  const size_t rs_words = (size_t)L.rs_parts * kMaxDigits;
-  L.table = take((rs_words > kg_rows * 256 ? rs_words : kg_rows * 256) * 4);
+  L.table = take((size_t)L.rs_parts * kMaxDigits * 4);
   L.totals = take(kMaxDigits * 4);
-  L.kg_counts = take(kg_rows * 4);
-  // the further chunks of at most `cap` instances
-  L.kg_list_max = (uint32_t)(cap / kKgChunk + 1);
-  L.kg_list = take((size_t)L.kg_list_max * 8);
+  L.kg_counts = take((size_t)((nn + kKgPart - 1) / kKgPart) * 4);
   L.count = take(4);
   L.tcls = take((size_t)kTileClasses * 4);
   L.tseg = take((size_t)kTileClasses * (tiles > 0 ? tiles : 1) * 4);
   L.bytes = o;
+  // The fused keygen's own buffers lie in those that are idle between the depth
+  // passes and the second tile pass, so that the finest slices cost no memory
+  // and the size never falls as n grows (a caller may size a workspace once,
+  // for its largest frame):
+  // - the slices' rows of up to 256 digits, where the radix table has too few
+  //   (only slices of 256 may need up to n + 255 words, from n = 513 on): in
+  //   dk[1] and dv[1] after it, 2 n words;
+  // - the places of the heavy slices' chunks, a word per slice: in dk[0];
+  // - the list of the further chunks of at most cap instances, 2 words each:
+  //   in tk[1], cap words (and at least 64).
+  const size_t kg_rows = (size_t)((nn + kg_part(nn, cap) - 1) / kg_part(nn, cap));
+  L.kg_table = kg_rows * 256 <= (size_t)L.rs_parts * kMaxDigits ? L.table : L.dk[1];
+  L.kg_base = L.dk[0];
+  L.kg_list_max = (uint32_t)(cap / kKgChunk + 1);
+  L.kg_list = L.tk[1];
   return L;
 }
 
@@ -1444,7 +1451,7 @@ SortLayout pairs_layout(int64_t n) {
   L.lookback = take((size_t)2 * L.parts * 256 * 4);
   L.table = take((size_t)L.rs_parts * kMaxDigits * 4);
   L.totals = take(kMaxDigits * 4);
-  L.kg_counts = L.kg_list = 0;
+  L.kg_counts = L.kg_table = L.kg_base = L.kg_list = 0;
   L.kg_list_max = 0;
   L.count = take(4);
   L.bytes = o;
@@ -1620,9 +1627,9 @@ hipError_t launch_keygen_fused(int64_t n, int64_t capacity, int bits, const uint
                                const uint32_t* vis_count, const uint2* rects,
                                uint2* sorted_rects, int tiles_x, const uint32_t* inst_count,
                                uint32_t* table, uint32_t* totals, uint32_t* heavy_count,
-                               uint32_t* kg_counts, uint2* kg_list, uint32_t kg_list_max,
+                               uint32_t* kg_base, uint2* kg_list, uint32_t kg_list_max,
                                uint32_t* tkeys, uint32_t* tvals, hipStream_t st) {
-  const KgHeavyK heavy{heavy_count, kg_counts, kg_list, kg_list_max};
+  const KgHeavyK heavy{heavy_count, kg_base, kg_list, kg_list_max};
   if (n == 0) return hipSuccess;
 #define GS_KF(B) kg_fused<B>(n, capacity, sorted_idx, vis_count, rects, sorted_rects, tiles_x, inst_count, table, totals, heavy, tkeys, tvals, st)
   switch (bits) {

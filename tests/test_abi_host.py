@@ -441,3 +441,39 @@ def test_batch_api_validation(lib):
     bad = L.GsAutotuneSpace()
     bad.n_orders = 7
     assert tune(space=bad) == L.GS_ERR_INVALID_ARGUMENT
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_sort_workspace_never_falls_with_n_or_capacity(lib, mode):
+    """A workspace sized once, for a caller's largest frame, is enough for every
+    smaller one: the size does not fall where the key generation changes its
+    slices."""
+    c, s = L.make_camera(S.pinhole_camera(S.look_at((0, 0, -8)), 640, 480)), L.default_settings(sort_mode=mode)
+    size = lambda n, cap: lib.gs_workspace_size(L.GS_STAGE_SORT, n, cap, ctypes.byref(c), ctypes.byref(s))
+    edges = [1, 256, 257, 512, 513, 131_072, 262_144, 270_000, 600_000, 1_300_000, 2_000_000]
+    ns = sorted({n + d for n in edges for d in (-1, 0, 1, 2, 255, 256)} - {0})
+    caps = sorted({1, 16_383, 16_384, 100_000, 300_000, *(2 * n + d for n in edges for d in (-1, 0, 1))})
+    table = [[size(n, cap) for n in ns] for cap in caps]
+    for cap, row in zip(caps, table):
+        for n, a, b in zip(ns[1:], row, row[1:]):
+            assert 0 < a <= b, (cap, n, a, b)
+    for cap, lo, hi in zip(caps[1:], table, table[1:]):
+        assert all(a <= b for a, b in zip(lo, hi)), cap
+
+
+@pytest.mark.parametrize("n_views", [1, 12, 16, 17, 32])
+def test_batch_workspace_never_falls_with_n(lib, n_views):
+    """The same for a batch, whose split of the views into workgroups changes
+    with n."""
+    cams = [L.make_camera(S.pinhole_camera(S.look_at((0, 0, -8)), 8, 8))] * n_views
+    s = L.default_settings()
+    last = 0
+    for n in [256 * b + d for b in range(1, 2400, 7) for d in (0, 1)]:
+        d, keep = batch_desc(n_views=n_views, n=n, cams=cams)
+        d.sh_degree = 3
+        h = ctypes.c_void_p()
+        assert lib.gs_batch_create(ctypes.byref(d), ctypes.byref(s), ctypes.byref(h)) == L.GS_OK
+        size = lib.gs_batch_workspace_size(h, 0)
+        lib.gs_batch_destroy(h)
+        assert size >= last, (n, last, size)
+        last = size

@@ -754,3 +754,38 @@ def test_heavy_keygen_slices(n, bits, short):
     full = last > first
     np.testing.assert_array_equal(rg[full], np.stack([first, last], 1)[full])
     assert np.all(rg[~full, 1] <= rg[~full, 0])
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 512, 513, 700, 20_000, 262_144])
+def test_sort_within_its_workspace(n):
+    """gs_sort stays within the bytes that gs_workspace_size states, with the
+    buffers that the key generation shares with the passes before and after it:
+    guard words behind the workspace keep their value, and the result equals
+    sort mode 1's, with the exact capacity and with ample capacity."""
+    import ctypes
+    from paper_2512_08478_amd import _lib as L
+    from paper_2512_08478_amd.render import GaussianParams, Renderer
+    print_case(f"sort within its workspace, n={n}")
+    sc, cam = S.tiny_scene(seed=9, n=n)
+    sc.log_scales[: min(n, 40)] = 1.0  # heavy slices
+    p = GaussianParams.from_scene(sc)
+    R0, R1 = (Renderer(dict(sort_mode=m, tile_w=8, tile_h=8)) for m in (0, 1))
+    pre = R1.preprocess(p, cam)
+    _, values, ranges, _, tot = R1.sort(n, *pre, cam)
+    want = u32(values).copy(), u32(ranges)[:2 * R1.tiles(cam)].copy()
+    lib, c = L.load(), L.make_camera(cam)
+    for cap in (tot, 3 * n + tot):
+        size = lib.gs_workspace_size(L.GS_STAGE_SORT, n, cap, ctypes.byref(c),
+                                     ctypes.byref(R0.settings))
+        guard = 1 << 20
+        ws = torch.full((size + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+        values = torch.zeros(cap, dtype=torch.int32, device="cuda")
+        ranges = torch.zeros(3 * R0.tiles(cam), dtype=torch.int32, device="cuda")
+        st = lib.gs_sort(n, *[t.data_ptr() for t in pre], ctypes.byref(c), ctypes.byref(R0.settings),
+                         cap, None, values.data_ptr(), ranges.data_ptr(), None, ws.data_ptr(), size,
+                         torch.cuda.current_stream().cuda_stream)
+        assert st == L.GS_OK
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all())
+        np.testing.assert_array_equal(u32(values)[:tot], want[0])
+        np.testing.assert_array_equal(u32(ranges)[:2 * R0.tiles(cam)], want[1])
