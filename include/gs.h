@@ -403,8 +403,9 @@ int32_t gs_sort_checked(int64_t n, const gs_splat* splats, const uint32_t* depth
  * for n Gaussians, `capacity` instances, this camera and these settings
  * (no HIP call; for tests and tools).  passes[0 .. *n_passes) in launch
  * order: the depth passes, then the tile passes (in sort mode 0 key
- * generation performs the first tile pass itself, and up to 16,384 Gaussians
- * one kernel, which counts each key's place, stands for the depth passes).
+ * generation performs the first tile pass itself).  In sort mode 0 the depth
+ * passes of at most 16,384 Gaussians, and at most 5,120 for each of them, are
+ * one kernel that counts each key's place: one pass of 32 bits here.
  * Each pass: its index
  * (also the parity of the look-back words it reads in mode 1: half
  * pass % 2), digit width, which count bounds its keys (GS_PASS_KEYS_ALL:
@@ -416,8 +417,8 @@ int32_t gs_sort_checked(int64_t n, const gs_splat* splats, const uint32_t* depth
  * A mode-1 pass reads words [0, partitions holding keys * 2^digit_bits) of
  * its half, publishes the same words, and clears words
  * [0, grid_partitions * 2^digit_bits) of the other half; gs_sort clears both
- * halves before the first pass.  GS_ERR_INVALID_ARGUMENT when more than
- * max_passes passes.
+ * halves before the first pass.  GS_ERR_INVALID_ARGUMENT when the depth and
+ * tile digits are more than max_passes.
  */
 typedef enum gs_pass_keys {
   GS_PASS_KEYS_ALL = 0,

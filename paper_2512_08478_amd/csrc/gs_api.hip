@@ -475,12 +475,14 @@ int32_t gs_preprocess_packed(int32_t n_assets, const gs_asset* assets, int64_t n
 }
 
 namespace {
-// The radix passes of one gs_sort call (shared by gs_sort and gs_sort_plan):
+// The passes of one gs_sort call (shared by gs_sort and gs_sort_plan):
 // depth passes first (all 32 bits in radix_bits-wide passes, or depth_bits
 // bits of the keys relative to the smallest visible key in balanced passes
-// of at most 9 bits in mode 0 / radix_bits in mode 1), then the tile passes.
+// of at most 9 bits in mode 0 / radix_bits in mode 1; or, of few Gaussians in
+// mode 0, one step that orders whole keys), then the tile passes.
 struct SortPlan {
   int pd = 0, pt = 0;
+  bool rank = false;  // the rank sort stands for the pd depth passes
   int widths[gs::kMaxPassTotal] = {};  // depth pass digit widths
 };
 
@@ -490,7 +492,7 @@ int tile_bits_of(int64_t tiles) {
   return b;
 }
 
-SortPlan plan_sort(int64_t tiles, const gs_settings* set) {
+SortPlan plan_sort(int64_t n, int64_t tiles, const gs_settings* set) {
   SortPlan P;
   const int bits = set->radix_bits, mode = set->sort_mode, db = set->depth_bits;
   if (db > 0 && mode == 0) {
@@ -505,6 +507,7 @@ SortPlan plan_sort(int64_t tiles, const gs_settings* set) {
   }
   const int tile_bits = tile_bits_of(tiles);
   P.pt = tile_bits > 0 ? (tile_bits + bits - 1) / bits : 1;
+  P.rank = mode == 0 && gs::rank_sort_fits(n, P.pd);
   return P;
 }
 }  // namespace
@@ -517,22 +520,23 @@ int32_t gs_sort_plan(int64_t n, int64_t capacity, const gs_camera* cam, const gs
   if (n < 0 || n >= kMaxN || capacity < 0 || capacity > kMaxInstances) return GS_ERR_INVALID_ARGUMENT;
   if (!passes || !n_passes || !lookback_words || max_passes < 0) return GS_ERR_INVALID_ARGUMENT;
   const int tiles = tiles_x_of(cam, set) * tiles_y_of(cam, set);
-  const SortPlan P = plan_sort(tiles, set);
+  const SortPlan P = plan_sort(n, tiles, set);
   if (P.pd + P.pt > max_passes) return GS_ERR_INVALID_ARGUMENT;
+  const int pd = P.rank ? 1 : P.pd;
   const gs::SortLayout L = gs::sort_layout(n, capacity, tiles);
   const int64_t part = set->sort_mode == 1 ? gs::kSortPart : 0;
-  for (int p = 0; p < P.pd + P.pt; ++p) {
+  for (int p = 0; p < pd + P.pt; ++p) {
     gs_sort_pass& o = passes[p];
-    const bool depth = p < P.pd;
+    const bool depth = p < pd;
     o.pass = p;
-    o.digit_bits = depth ? P.widths[p] : set->radix_bits;
+    o.digit_bits = !depth ? set->radix_bits : P.rank ? 32 : P.widths[p];
     o.keys = depth ? (p == 0 ? GS_PASS_KEYS_ALL : GS_PASS_KEYS_VISIBLE) : GS_PASS_KEYS_INSTANCES;
     o.partition_keys = (int32_t)part;
     const int64_t grid_n = depth ? n : capacity;
     o.grid_partitions = part > 0 ? (int32_t)((grid_n + part - 1) / part) : 0;
   }
   // in mode 0 the key generation writes the first tile pass's output itself
-  *n_passes = P.pd + P.pt;
+  *n_passes = pd + P.pt;
   *lookback_words = set->sort_mode == 1 ? (int64_t)2 * L.parts * 256 : 0;
   return GS_OK;
 }
@@ -571,7 +575,7 @@ int32_t sort_impl(int64_t n, const gs_splat* splats, const uint32_t* depth_keys,
   const int bits = set->radix_bits, mode = set->sort_mode;
   const bool heavy_first = (set->raster_order & 1) != 0;
   const int db = set->depth_bits;
-  const SortPlan plan = plan_sort(tiles, set);
+  const SortPlan plan = plan_sort(n, tiles, set);
   const int* widths = plan.widths;
   const int pd = plan.pd, pt = plan.pt;
   char* ws = static_cast<char*>(workspace);
@@ -615,7 +619,7 @@ int32_t sort_impl(int64_t n, const gs_splat* splats, const uint32_t* depth_keys,
   if (fold_init)
     d.init = gs::sort_init_args(L, ws, tile_ranges, tiles, status_flag, counts, capacity,
                                 heavy_first ? U(L.tcls) : nullptr, db);
-  if (mode == 0 && gs::rank_sort_fits(n, pd))
+  if (plan.rank)
     e = gs::launch_rank_sort(n, depth_keys, nullptr, 1, nullptr, d.v_out, d.init, "depth_pass", st);
   else if (mode == 0)
     e = gs::launch_radix_sort_widths(d, widths, pd, false, "depth_pass", st);

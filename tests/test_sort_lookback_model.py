@@ -97,3 +97,20 @@ def test_plan_matches_key_bits():
         assert sum(p["digit_bits"] for p in depth) >= 32
         assert len(tile) == -(-(kb - 32) // 7)
         assert (words > 0) == (mode == 1)
+
+
+@pytest.mark.parametrize("db,passes", [(0, 4), (25, 3), (9, 1), (10, 2)])
+def test_plan_of_few_gaussians_is_one_depth_pass(db, passes):
+    """Mode 0 sorts the depths of few Gaussians (at most 16,384, and 5,120 for
+    each radix pass) in one step, and the plan says so; mode 1 always makes its
+    radix passes."""
+    most = min(16_384, 5_120 * passes)
+    for mode in (0, 1):
+        s = L.default_settings(sort_mode=mode, depth_bits=db)
+        for n in (0, 1, most, most + 1):
+            plan, _ = L.sort_plan(n, 5000, CAMS["1080p"], s)
+            depth = [p for p in plan if p["keys"] != L.GS_PASS_KEYS_INSTANCES]
+            if mode == 0 and n <= most:
+                assert [p["digit_bits"] for p in depth] == [32]
+            else:
+                assert len(depth) == (passes if mode == 0 else -(-(db or 32) // 8))
