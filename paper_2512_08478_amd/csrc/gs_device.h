@@ -14,6 +14,17 @@ __device__ __forceinline__ int lane_id() {
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
+// Orders a wave's LDS accesses: what its lanes stored before is there for
+// every lane after, and loads before are done with what stores after overwrite.
+// The hardware runs a wave's LDS accesses in order, so this costs no
+// instruction: it keeps the compiler, which sees one lane at a time, from moving
+// accesses to what for that lane are different addresses.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // bits of lanes below this one
 __device__ __forceinline__ uint64_t lanemask_lt() {
   const int l = lane_id();

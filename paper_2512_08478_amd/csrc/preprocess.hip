@@ -226,12 +226,14 @@ __device__ __forceinline__ void preprocess_block(
         const int f = lane + 64 * k;
         if (f < kShRows * F4) buf[f] = pre[h][k];
       }
+      wave_lds_sync();
       if (tiles > 0 && lane / kShRows == h) {
         float Y[16], rgb[3];
         sh_basis<DEG>(dir[0], dir[1], dir[2], Y);
         row_colour<DEG>(buf + (lane - h * kShRows) * F4, Y, rgb);
         set_colour(rgb, r1, r2);
       }
+      wave_lds_sync();
     }
   }
   if (i < n) {
@@ -299,6 +301,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
       const int f = lane + 64 * k;
       if (f < len) rows[f / F4 * STRIDE + f % F4] = src[f];
     }
+    wave_lds_sync();
   }
   uint32_t tot = 0, vis = 0, kmin = 0xFFFFFFFFu, kmax = 0;
   if (i < n) {
