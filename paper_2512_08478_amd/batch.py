@@ -34,23 +34,32 @@ SORT_MODES = (0, 1)
 RASTER_ORDERS = (1, 0, 3, 5, 2, 4)
 
 
+def _nothing_watches():
+    """Whether nothing records or transforms torch's operations (torch.func,
+    forward-mode differentiation, dispatch and function modes, tracing).  torch
+    has no public names for some of these: without one of them nothing is known,
+    and the answer is no."""
+    try:
+        return (torch._C._functorch.peek_interpreter_stack() is None and
+                torch.autograd.forward_ad._current_level < 0 and
+                torch._C._len_torch_dispatch_stack() == 0 and
+                torch._C._len_torch_function_stack() == 0 and
+                not torch.jit.is_tracing() and not torch.compiler.is_compiling())
+    except (AttributeError, TypeError):
+        return False
+
+
 def _l1_in_kernel(image, target, H, W):
     """Whether gs_l1_grad computes l1_grad(image, target): plain float32
-    tensors of the frame's layout on the current device, with nothing that
-    records or transforms the operations (autograd, torch.func, dispatch
-    modes, tracing)."""
+    tensors of the frame's layout on the current device, without autograd, and
+    nothing watches the operations."""
     for t in (image, target):
         if type(t) is not torch.Tensor or t.dtype != torch.float32 or t.requires_grad:
             return False
     return (0 < H * W < 2**31 and target.shape == (H, W, 3) and image.shape == (H, W, 4) and
             image.is_cuda and target.device == image.device and
             image.device.index == torch.cuda.current_device() and
-            torch._C._functorch.peek_interpreter_stack() is None and
-            torch.autograd.forward_ad._current_level < 0 and
-            torch._C._len_torch_dispatch_stack() == 0 and
-            torch._C._len_torch_function_stack() == 0 and
-            not torch.jit.is_tracing() and not torch.compiler.is_compiling() and
-            image.is_contiguous() and target.is_contiguous() and
+            _nothing_watches() and image.is_contiguous() and target.is_contiguous() and
             not image.is_neg() and not target.is_neg() and image.data_ptr() % 16 == 0)
 
 

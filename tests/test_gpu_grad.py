@@ -292,3 +292,22 @@ def test_gradient_records_elementwise(kind):
     for nm, a, b in zip(("mx", "my", "qa", "qb", "qc", "o", "r", "g", "b"), rms(got), ratio):
         print(f"{nm}: rms error {a:.2e} of the terms' magnitudes, {b:.2f} times plain float32's")
     assert ratio.max() <= 2.0
+
+
+@pytest.mark.parametrize("owner,name", [
+    ("_C._functorch", "peek_interpreter_stack"), ("autograd.forward_ad", "_current_level"),
+    ("_C", "_len_torch_dispatch_stack"), ("_C", "_len_torch_function_stack")])
+def test_l1_grad_without_torchs_private_names(monkeypatch, owner, name):
+    """On a torch without one of the private names that tell whether the
+    operations are watched, l1_grad takes its elementwise form."""
+    import functools
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_08478_amd.batch import l1_grad
+    print_case(f"l1 gradient without torch.{owner}.{name}")
+    image, target = torch.rand(5, 7, 4, device="cuda"), torch.rand(5, 7, 3, device="cuda")
+    want = l1_grad(image, target)
+    monkeypatch.delattr(functools.reduce(getattr, owner.split("."), torch), name)
+    got = l1_grad(image, target)
+    monkeypatch.undo()
+    assert torch.equal(got, want)
