@@ -277,7 +277,7 @@ def make_camera(cam) -> GsCamera:
         return cam
     c = GsCamera()
     vm = cam.viewmat
-    if isinstance(vm, np.ndarray) and vm.ndim <= 2:
+    if type(vm) is np.ndarray and vm.ndim <= 2 and vm.dtype.kind in "biuf":
         vm = vm.ravel().tolist()
     elif hasattr(vm[0], "__len__"):
         vm = [float(x) for row in vm for x in row]

@@ -477,3 +477,23 @@ def test_batch_workspace_never_falls_with_n(lib, n_views):
         lib.gs_batch_destroy(h)
         assert size >= last, (n, last, size)
         last = size
+
+
+def test_make_camera_takes_what_float_takes():
+    """A view matrix is read element by element through float(), whatever holds
+    it; numeric arrays, which are read at once, give the same numbers."""
+    import numpy as np
+    cam = S.pinhole_camera(S.look_at((0.3, 0.1, -8)), 640, 480)
+    base = np.asarray(cam.viewmat, np.float64)
+    want = [float(np.float32(x)) for x in base.ravel()]
+    same = [base, base.astype(np.float32), base.tolist(), base.ravel(), base.ravel().tolist(),
+            base.astype(object), base.astype(str), np.asfortranarray(base), base[::1, ::1],
+            [[str(x) for x in row] for row in base]]
+    for vm in same:
+        cam.viewmat = vm
+        got = list(L.make_camera(cam).viewmat)
+        assert got == pytest.approx(want, abs=1e-7), type(vm)
+    for vm in (np.matrix(base), base[:3], 7.0):
+        cam.viewmat = vm
+        with pytest.raises((TypeError, IndexError)):
+            L.make_camera(cam)
