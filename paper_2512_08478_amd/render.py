@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 from dataclasses import dataclass
+from operator import index
 
 import torch
 
@@ -328,6 +329,7 @@ class Renderer:
         see mesh_buffers)."""
         if mesh is not None:
             mesh = mesh_buffers(mesh, cam, self.device)
+        index(cam.width), index(cam.height)  # whole numbers only: make_camera would cut them
         cam = L.make_camera(cam)
         splats, dkeys, rects, counts = self.preprocess(p, cam, reuse)
         keys, values, ranges, flag, cap = self.sort(p.n, splats, dkeys, rects, counts, cam, capacity,

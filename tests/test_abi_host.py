@@ -497,3 +497,15 @@ def test_make_camera_takes_what_float_takes():
         cam.viewmat = vm
         with pytest.raises((TypeError, IndexError)):
             L.make_camera(cam)
+
+
+def test_forward_takes_whole_pixel_counts_only():
+    """A frame size that is no whole number is refused, not cut (before any
+    buffer is made or any call reaches the library)."""
+    from paper_2512_08478_amd.render import GaussianParams, Renderer
+    sc, cam = S.tiny_scene(n=4)
+    p = GaussianParams.from_scene(sc, device="cpu")
+    for size in ((256.5, 256), (256, 255.0)):
+        cam.width, cam.height = size
+        with pytest.raises(TypeError):
+            Renderer(device="cpu").forward(p, cam, capacity=4)
