@@ -673,36 +673,42 @@ __device__ __forceinline__ uint32_t block_excl_max(uint32_t v, uint32_t* s_tmp) 
 
 constexpr int kKgWin = 2048;              // instances expanded per window
 constexpr int kKgWinItems = kKgWin / kBlock;
-// The fused keygen cuts the depth-sorted Gaussians into slices of PART; a
-// workgroup of NT threads expands its slice's instances window by window, one
+// The fused keygen cuts the depth-sorted visible Gaussians into slices of PART;
+// a workgroup of NT threads expands its slice's instances window by window, one
 // after another.  While all slices fit on the GPU at once the kernel lasts as
 // long as its heaviest slice (the nearest, largest Gaussians), which finer
 // slices and more threads per instance shorten; but each slice costs a
-// prologue and a row of digit counts to scan.  Histogram, scan and scatter of
-// 16x16-tile frames at 1920x1080 (~3.4 instances per Gaussian) and at 66x49
-// (~0.9), 8-bit digits, us (slices of 1,024 with 512 threads in brackets):
-//   up to kKgFineMaxN Gaussians  256, NT 256, windows of 1,024
-//                                (60k: 30.9 (45.6) and 21.0 (22.3), 250k:
-//                                36.4 (51.1) and 25.3 (23.7))
-//   up to kKgMidMaxN, and up to  512, NT 512, windows of 2,048
-//   kKgMidDenseMaxN where there  (400k: 41.5 (55.2) and 29.8 (28.8), 900k:
-//   is room for two instances    54.2 (62.4) and 43.8 (37.2), 1.1M: 61.4
-//   per Gaussian                 (66.2) and 48.7 (40.0))
-//   up to kKgWideMaxN            1,024, NT 512 (1.9M: 86.6 and 58.8; with
-//                                slices of 512, 93.4 and 71.3)
-//   beyond                       1,024, NT 256: the slices come in several
-//                                rounds anyway (6M: 146 us; with slices of
-//                                512, 161 us).
+// prologue and a row of digit counts to scan, for which there must be instances
+// enough.  Histogram, scan and scatter, 16x16 tiles, 8-bit digits, us with
+// slices of 256 (NT 256, windows of 1,024) / 512 (NT 512, windows of 2,048) /
+// 1,024 (NT 512, windows of 2,048):
+//   Gaussians    0.93       1.3        1.8        2.4        3.4 instances each
+//   100k       22/22/23   22/22/27   25/26/34   28/30/39   31/35/47
+//   180k       23/23/24   24/24/27   26/27/35   29/31/39   33/36/51
+//   262k       26/26/24   27/26/28   29/29/35   31/32/40   36/37/52
+//   350k       29/27/25   30/27/29   31/30/37   34/34/43   38/40/55
+//   500k       35/31/30   36/32/31   37/34/39   38/36/43   43/41/55
+//   700k       41/37/31   42/37/33   42/38/40   44/41/45   47/44/56
+//   900k       47/43/37   48/44/39   50/46/46   50/48/49   55/52/60
+//   1.2M       56/53/45   57/52/46   59/53/52   60/57/54   67/62/66
+// So: 256 up to 262,144 Gaussians where at most 180,000 can be visible (no more
+// than there are instances) or there are 9 instances or more to 8 Gaussians; with
+// as many, 512 up to 1.3M Gaussians where each has n / 400,000 instances or more;
+// else 1,024.  Beyond 2M Gaussians the slices come in several rounds anyway, and
+// NT 256 is enough (6M: 146 us; with slices of 512, 161 us).
 // The histogram walks each rect's tile rows in one thread; its workgroup has
 // a thread per Gaussian, which spreads a slice's large rects.
 constexpr int kKgFinePart = 256, kKgFineThreads = 256, kKgFineWin = 1024;
-constexpr int64_t kKgFineMaxN = 262144;
+constexpr int64_t kKgFineMaxN = 262144, kKgFineVisible = 180000;
 constexpr int kKgMidPart = 512, kKgMidThreads = 512;
-constexpr int64_t kKgMidMaxN = 600000, kKgMidDenseMaxN = 1300000;
+constexpr int64_t kKgMidMaxN = 1300000, kKgMidPerInstance = 400000;
 constexpr int64_t kKgWideMaxN = 2000000;
 int kg_part(int64_t n, int64_t capacity) {
-  if (n <= kKgFineMaxN) return kKgFinePart;
-  return n <= kKgMidMaxN || (n <= kKgMidDenseMaxN && capacity >= 2 * n) ? kKgMidPart : kKgPart;
+  const bool dense = 8 * capacity >= 9 * n;
+  if (n <= kKgFineMaxN)
+    return dense || (n < capacity ? n : capacity) <= kKgFineVisible ? kKgFinePart : kKgPart;
+  const bool mid = dense && n <= kKgMidMaxN && capacity >= n * n / kKgMidPerInstance;
+  return mid ? kKgMidPart : kKgPart;
 }
 constexpr int kKgScatThreads = 256;
 constexpr int kKgScatWin = 2048;

@@ -789,3 +789,41 @@ def test_sort_within_its_workspace(n):
         assert bool((ws[size:] == 0x5A).all())
         np.testing.assert_array_equal(u32(values)[:tot], want[0])
         np.testing.assert_array_equal(u32(ranges)[:2 * R0.tiles(cam)], want[1])
+
+
+def sorted_in_both_modes(n, scene, cam, capacity=None, **over):
+    """(sorted keys, values, ranges, flag) of sort modes 0 and 1 for the
+    capacity (None: the instance count)."""
+    from paper_2512_08478_amd.render import GaussianParams, Renderer
+    p = GaussianParams.from_scene(scene)
+    got = []
+    for mode in (0, 1):
+        Rm = Renderer(dict(over, sort_mode=mode))
+        pre = Rm.preprocess(p, cam)
+        tot = int(u32(pre[3])[0])
+        cap = tot if capacity is None else capacity
+        assert cap >= tot
+        keys, values, ranges, flag, _ = Rm.sort(n, *pre, cam, capacity=cap, want_keys=True)
+        torch.cuda.synchronize()
+        got.append((u64(keys)[:tot], u32(values)[:tot], u32(ranges)[:2 * Rm.tiles(cam)], u32(flag)))
+    return got, tot
+
+
+@pytest.mark.parametrize("n,per_gaussian", [
+    (180_000, 1.0), (180_001, 1.0), (180_001, 1.126), (262_144, 1.124), (262_144, 1.126),
+    (262_145, 1.124), (262_145, 1.126), (600_000, 1.499), (600_000, 1.501), (600_001, 1.501),
+    (1_300_000, 3.249), (1_300_000, 3.251), (1_300_001, 3.251)])
+def test_keygen_slice_rule(n, per_gaussian):
+    """The key generation's slices (256, 512 or 1,024 Gaussians) follow n and the
+    instance capacity: on both sides of each limit, keys, values and ranges equal
+    those of sort mode 1, whose key generation has slices of one size."""
+    print_case(f"keygen slice rule n={n}, capacity {per_gaussian} n")
+    sc, _ = S.tiny_scene(seed=6, n=n)
+    cam = S.pinhole_camera(S.look_at((0.0, 0.0, -3.0)), 1024, 1024, 60.0)
+    sc.log_scales[:] = -9.0
+    sc.log_scales[:: n // 300] = -2.0
+    sc.means[::4, 2] = -9.0  # behind the camera
+    got, tot = sorted_in_both_modes(n, sc, cam, int(per_gaussian * n), tile_w=32, tile_h=32)
+    assert tot > 0.6 * n
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
