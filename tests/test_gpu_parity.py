@@ -827,3 +827,31 @@ def test_keygen_slice_rule(n, per_gaussian):
     assert tot > 0.6 * n
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,bits,width", [(700, 6, 1600), (700, 8, 6400), (200_000, 6, 1600),
+                                          (300_000, 6, 1600), (300_000, 8, 6400),
+                                          (1_400_000, 7, 3200)])
+def test_heavy_slices_on_wide_grids(n, bits, width):
+    """Splats over whole rows of grids that are several times as wide as the
+    first digit's range (slices of 256, 512 and 1,024): each row turns the digit
+    round more than once, and the chunks of 16,384 instances that heavy slices
+    are expanded in end within rows.  Against sort mode 1."""
+    print_case(f"heavy slices, {width // 8} tiles wide, {bits} bits, n={n}")
+    sc, _ = S.tiny_scene(seed=8, n=n)
+    cam = S.pinhole_camera(S.look_at((0.0, 0.0, -3.0)), width, 264, 20.0)
+    rng = np.random.default_rng(n + bits)
+    sc.log_scales[:] = -9.0
+    heavy = rng.permutation(min(n, 700))[:160]
+    sc.means[heavy] = rng.uniform(-0.05, 0.05, (160, 3)) + np.array([0.0, 0.0, -1.9])
+    sc.log_scales[heavy] = np.stack([np.full(160, 2.0), rng.uniform(-4.0, 0.0, 160),
+                                     np.full(160, -4.0)], 1)
+    sc.quats[heavy] = np.array([1.0, 0.0, 0.0, 0.0])
+    sc.opacity_logits[heavy] = 2.0
+    tiles_x = width // 8
+    assert tiles_x >= 2 << bits
+    got, tot = sorted_in_both_modes(n, sc, cam, radix_bits=bits, tile_w=8, tile_h=8)
+    row = (got[0][0] >> np.uint64(32)).astype(np.int64) // tiles_x
+    assert tot > 8 * 16384 and np.bincount(row).min() >= tiles_x
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
