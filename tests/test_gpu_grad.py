@@ -311,3 +311,37 @@ def test_l1_grad_without_torchs_private_names(monkeypatch, owner, name):
     got = l1_grad(image, target)
     monkeypatch.undo()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n", [1, 6, 7, 8, 14, 15, 31, 32, 33, 63, 64, 65, 97, 200])
+def test_backward_groups_in_ragged_quadrants(R, orc, n):
+    """The compositing backward sums groups of 7 visited splats, from lists of 32
+    staged ones, from batches of 64: n faint splats that every pixel of a 19x17
+    frame blends, those of the quadrants of 3 columns and of 1 row included.
+    Tolerance, of a gradient's norm: 26 roundings of 2^-24 in each pixel's terms
+    and their sums, 5 more for each splat in the transmittance and the colour
+    behind that the walk recovers, and 10-fold cancellation in the chain rule (a
+    splat left out or counted twice is 1 / n, 8 times as much or more)."""
+    print_case(f"backward, {n} Gaussians blended into every pixel")
+    from oracle import grad as og
+    rng = np.random.default_rng(300 + n)
+    sc, _ = S.fd_scene(seed=40 + n, n=n, size=32)
+    cam = S.pinhole_camera(S.look_at((0.0, 0.0, -3.0)), 19, 17, 60.0)
+    sc.means[:] = 0.15 * sc.means
+    sc.log_scales[:] = rng.normal(1.2, 0.15, (n, 3))
+    sc.opacity_logits[:] = rng.normal(-3.8, 0.1, n)
+    pix = orc.all_pixels(cam)
+    ref = orc.render_pixels(orc.preprocess(sc, cam), cam, pix)
+    G = rng.standard_normal((len(pix), 4))
+    near = (ref["margin"] < 1e-4) | (ref["flags"] != 0)
+    G[near] = 0.0
+    assert near.mean() < 0.2
+    _, g_ref = og.render_and_grad(sc, cam, pix, G)
+    fr, g = gpu_grads(R, sc, cam, G.reshape(cam.height, cam.width, 4))
+    count = torch.zeros((cam.height, cam.width), dtype=torch.int32, device="cuda")
+    R.rasterize(fr.splats, fr.values, fr.ranges, cam, n_blend=count)
+    assert bool((count == n).all())
+    for nm in NAMES:
+        e = rel_l2(g[nm], g_ref[nm])
+        print(f"{nm}: rel L2 {e:.2e}")
+        assert e <= 10 * (26 + 5 * n) * 2.0 ** -24, (nm, e)
