@@ -635,7 +635,7 @@ int32_t gs_l1_grad(int64_t n_pixels, const float* image, const float* target, fl
  * widest view, so a key is band row * width + column), one compositing
  * launch over every view's tiles (longest lists first, over all views),
  * and with targets one loss-gradient launch, one compositing-backward
- * launch and the chain rule (one launch per asset and 8 views).  Counts are
+ * launch and one launch of the chain rule over all assets and views.  Counts are
  * read on the device; only gs_batch_plan syncs.  Images equal those of
  * single-view calls with the same settings, bit for bit.
  *

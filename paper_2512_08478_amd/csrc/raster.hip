@@ -509,7 +509,7 @@ __global__ __launch_bounds__(64) void k_raster(const gs_splat* __restrict__ spla
 //
 // Bound: vector issue.  With each splat's 9 values formed, exchanged and sent
 // as soon as it was visited, a visit took ~130 vector instructions; here ~55,
-// and its share of a group ~11.  Measured: 500k Gaussians at 800x800, 32x16
+// and its share of a group ~7.  Measured: 500k Gaussians at 800x800, 32x16
 // tiles, 247 -> 208 us; 32 views of 4.5M, 16x8 tiles, 11.9 -> 9.6 ms; 20k at
 // 250x190, 138 -> 98 us.
 //
